@@ -152,19 +152,21 @@ int lbm_hydrostatic_pressure(const lbm_params *p, const void *phi0, void *p0, vo
 /* Advance nsteps >= 0 time steps (Sec. 3): moments, closure, both MRT
  * collisions and streaming with bounce-back, fused in one kernel per step --
  * or per two steps, for the Allen-Cahn step with stencil or local gradients
- * (present and original models) on a lattice of at least 256 tiles of 64 x 8
- * nodes whose state copy is below 4 GiB, cache-resident or streamed from HBM
- * (lbm_levels_per_launch; the environment variable LBM_TWO_LEVEL = "0" or "1"
- * turns the size rule off or on for every such state): a run of n steps is
- * then n / 2 two-level launches and, for odd n, one one-level launch, with
+ * (present and original models) on a lattice whose state copy is below 4 GiB,
+ * cache-resident or streamed from HBM (the environment variable LBM_TWO_LEVEL =
+ * "0" turns this off): a run of n steps is then n / 2 two-level launches and,
+ * for odd n, one one-level launch, with
  * results equal bit for bit to n one-level launches.  On a non-NULL stream, runs of >= 64 steps
  * replay a captured graph of 32 steps (cached per params, state and stream);
  * while the caller captures the stream itself, the kernels are launched into
  * the caller's graph instead.  Every option. */
 int lbm_step(const lbm_params *p, void *state, int64_t nsteps, void *stream);
 
-/* Time levels that one step launch of lbm_step advances for these params
- * (1 or 2; see lbm_step).  Host only, no device work. */
+/* Time levels per crossing of the state (1 or 2): 2 where lbm_step folds two
+ * levels into a launch on a lattice of at least 256 tiles of 64 x 8 nodes, or on
+ * any lattice with LBM_TWO_LEVEL = "1" in the environment.  Smaller lattices
+ * report 1: their launches are bound by latency, not by the bytes of a level,
+ * and lbm_step folds levels there as it finds best.  Host only, no device work. */
 int lbm_levels_per_launch(const lbm_params *p, int32_t *levels /* host */);
 
 /* Order parameter, velocity (Eq. comU) and pressure (Eq. computP) of the

@@ -213,15 +213,15 @@ void k_tape_step(KParams<T> P, char* tape, size_t slot, int j, int ntx, int nty)
 // intermediate level, stored non-temporally: the adjoint reads it back later)
 // and slot j + 2, on the lattices where lbm_step takes two levels per launch;
 // bitwise the levels of two k_tape_step launches.
-template <typename T, int TY, int NBY, bool STD, bool NTS>
-__global__ __launch_bounds__(TX* NBY) void k_tape_step2(KParams<T> P, char* tape, size_t slot, int j, int ntx,
-                                                         int nty) {
-    __shared__ Step2Lds<T, TY> L;
+template <typename T, int TW, int TY, int NT, bool STD, bool NTS>
+__global__ __launch_bounds__(NT) void k_tape_step2(KParams<T> P, char* tape, size_t slot, int j, int ntx, int nty) {
+    __shared__ Step2Lds<T, TW, TY> L;
     const int64_t n = reinterpret_cast<const TapeHeader*>(tape)->n0 + j;
     char* src = tape + TAPE_HDR + (size_t)j * slot;
     int xt, yt;
     xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_mid<T, TY, NBY, STD, NTS>(P, src, src + slot, src + 2 * slot, n, xt, yt, L);
+    step2_body<T, TW, TY, NT, STD, NTS, true>((ParamsPtr<T>)__builtin_amdgcn_kernarg_segment_ptr(),
+                                              TapeTile{src, src + slot, src + 2 * slot, n, xt, yt}, L);
 }
 
 // ---------------------------------------------------------------- adjoint step, kernel A
@@ -805,30 +805,31 @@ static void tape_step_launch(const KParams<T>& P, char* tape, size_t slot, int j
     }
 }
 
-template <typename T, int TY, int NBY>
+template <typename T, int TW, int TY, int NT>
 static void tape_step2_launch(const KParams<T>& P, char* tape, size_t slot, int j, hipStream_t s) {
-    const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
-    const dim3 blk(TX, NBY);
+    const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
+    const dim3 blk(TX, NT / TX);
+    auto go = [&](auto kernel) { kernel<<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty); };
     // slot j + 2 with ordinary stores while it and the next fit the last-level cache (the next launch reads it)
-    if (2 * slot <= (size_t)LBM_NT_MIN_BYTES) {
-        if (P.rates_std) k_tape_step2<T, TY, NBY, true, false><<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty);
-        else k_tape_step2<T, TY, NBY, false, false><<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty);
-    } else {
-        if (P.rates_std) k_tape_step2<T, TY, NBY, true, true><<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty);
-        else k_tape_step2<T, TY, NBY, false, true><<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty);
-    }
+    const bool cached = 2 * slot <= (size_t)LBM_NT_MIN_BYTES;
+    if (P.rates_std) cached ? go(k_tape_step2<T, TW, TY, NT, true, false>) : go(k_tape_step2<T, TW, TY, NT, true, true>);
+    else cached ? go(k_tape_step2<T, TW, TY, NT, false, false>) : go(k_tape_step2<T, TW, TY, NT, false, true>);
 }
 
-// The tile rows of the two-level launch of lbm_step (lbm_step2.hip).
+// The tiles of the two-level launch of lbm_step (step2_shape).
 template <typename T>
 static void tape_step2(const KParams<T>& P, char* tape, size_t slot, int j, hipStream_t s) {
-    const long long ntx = (P.nx + TX - 1) / TX;
-    const long long t8 = ntx * ((P.ny + 7) / 8), t16 = ntx * ((P.ny + 15) / 16);
-    if constexpr (sizeof(T) == 4) {
-        if (t16 <= 256 && t8 > 256) tape_step2_launch<T, 16, 16>(P, tape, slot, j, s);
-        else tape_step2_launch<T, 8, 8>(P, tape, slot, j, s);
-    } else {
-        tape_step2_launch<T, 8, 8>(P, tape, slot, j, s);
+    switch (step2_shape(P.nx, P.ny, sizeof(T), 2 * slot <= (size_t)LBM_NT_MIN_BYTES)) {
+        case S2_16x4: tape_step2_launch<T, 16, 4, 256>(P, tape, slot, j, s); break;
+        case S2_32x4: tape_step2_launch<T, 32, 4, 384>(P, tape, slot, j, s); break;
+        case S2_32x8_WIDE: tape_step2_launch<T, 32, 8, 576>(P, tape, slot, j, s); break;
+        case S2_32x16: tape_step2_launch<T, 32, 16, 512>(P, tape, slot, j, s); break;
+        case S2_64x16:
+            if constexpr (sizeof(T) == 4) tape_step2_launch<T, 64, 16, 1024>(P, tape, slot, j, s);
+            break;
+        default:
+            if constexpr (sizeof(T) == 8) tape_step2_launch<T, 32, 8, 256>(P, tape, slot, j, s);
+            else tape_step2_launch<T, 64, 8, 512>(P, tape, slot, j, s);
     }
 }
 
@@ -896,7 +897,7 @@ int lbm_tape_record(const lbm_params* p, const void* state, void* tape, int32_t 
                                                                        p->nx, p->ny, p->dtype);
     int ty, by;
     step_shape(p, &ty, &by);
-    const bool two = two_level_path(L, p->nx, p->ny, p->phase_eq, p->model, p->grad_scheme);
+    const bool two = two_level_step(L, p->nx, p->ny, p->phase_eq, p->model);
     if (p->dtype == LBM_F32)
         launch_tape_steps<float>(resolve<float>(p, L), (char*)tape, L.buf_bytes, nlevels, two, ty, by, s);
     else

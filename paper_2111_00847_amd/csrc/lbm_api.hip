@@ -376,7 +376,7 @@ int lbm_levels_per_launch(const lbm_params* p, int32_t* levels) {
     int rc = validate(p);
     if (rc) return rc;
     if (!levels) return LBM_E_NULL;
-    *levels = two_level_path(layout_of(p), p->nx, p->ny, p->phase_eq, p->model, p->grad_scheme) ? 2 : 1;
+    *levels = two_level_path(layout_of(p), p->nx, p->ny, p->phase_eq, p->model) ? 2 : 1;
     return LBM_OK;
 }
 

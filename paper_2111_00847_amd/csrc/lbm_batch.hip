@@ -47,6 +47,7 @@ struct BatchCase {
     size_t base;                 // byte offset of the case's state in the batch buffer
     size_t off0, off1, off_stamp;
     int ntx, nty;
+    StampShare share;            // of the case's tiles (two-level launch)
     int item_begin;              // first work item of this case
     int body;                    // 0: Allen-Cahn step; 1: Cahn-Hilliard; 2: corrected Allen-Cahn (ACC);
                                  // 3: Allen-Cahn with the local gradient scheme
@@ -108,17 +109,15 @@ void k_step_batch(const BatchCase<T>* __restrict__ cases, int ncases, int nitems
 template <typename T, bool NTS, bool PER_ITEM = false>
 __global__ __launch_bounds__(TX * 8) void k_step2_batch(const BatchCase<T>* __restrict__ cases, int ncases,
                                                        int nitems, char* batch_state) {
-    __shared__ Step2Lds<T, 8> L;
+    __shared__ Step2Lds<T, TX, 8> L;
     const int w = blockIdx.x;
     if (w >= nitems) return;   // uniform over the workgroup
     const BatchCase<T>& C = cases[PER_ITEM ? w : batch_case(cases, ncases, w, TX * 8)];
     const int local = w - C.item_begin;
-    if (C.P.rates_std)
-        step2_tile<T, 8, 8, true, NTS>(C.P, batch_state + C.base, C.off0, C.off1, C.off_stamp, local % C.ntx,
-                                       local / C.ntx, L);
-    else
-        step2_tile<T, 8, 8, false, NTS>(C.P, batch_state + C.base, C.off0, C.off1, C.off_stamp, local % C.ntx,
-                                        local / C.ntx, L);
+    const StateTile tile{batch_state + C.base, C.off0, C.off1, C.off_stamp, C.share, local, local % C.ntx,
+                         local / C.ntx, 0};
+    if (C.P.rates_std) step2_body<T, TX, 8, TX * 8, true, NTS>((ParamsPtr<T>)&C.P, tile, L);
+    else step2_body<T, TX, 8, TX * 8, false, NTS>((ParamsPtr<T>)&C.P, tile, L);
 }
 
 // Batches with two-node-window or local-gradient cases: 64 x TY threads (one
@@ -235,7 +234,9 @@ int fill_cases(const lbm_params* params, const Layout* layouts, const size_t* ba
                  : q.model == LBM_MODEL_CORRECTED ? 2
                  : q.grad_scheme == LBM_GRAD_LOCAL ? 3
                                                    : 0;
-        items += tiles_for(params[c], ty, &C.ntx, &C.nty);
+        const int tiles = tiles_for(params[c], ty, &C.ntx, &C.nty);
+        C.share = stamp_share((long long)layouts[c].nstamp, tiles);
+        items += tiles;
     }
     return items;
 }

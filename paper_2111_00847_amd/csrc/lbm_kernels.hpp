@@ -13,10 +13,52 @@ hipError_t launch_step(const KParams<T>& P, char* state, const Layout& L, int64_
 // two levels of the plain Allen-Cahn step in one launch (lbm_step2.hip)
 template <typename T>
 void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s);
+// A tile of the two-level launch owns at least one level stamp (lbm_step2.hpp).
+inline bool stamp_share_ok(int nx, int ny, int tw, int ty) {
+    const long long nstamp = (long long)((nx + STAMP_BAND - 1) / STAMP_BAND) * ny;
+    return nstamp >= (long long)((nx + tw - 1) / tw) * ((ny + ty - 1) / ty);
+}
+
+// Tiles of the two-level launch.  A tile's chain (loads, level n, level n + 1)
+// sets the launch's duration until every CU has several of them, so a lattice
+// takes the smallest tiles that leave no CU with two; beyond one round the ring
+// (region nodes per tile node: 16 x 4 2.5, 32 x 4 2.25, 32 x 8 1.69, 32 x 16 1.41,
+// 64 x 8 1.59, 64 x 16 1.33) and the workgroups a CU holds decide.  Measured on
+// MI355X, us per level, chosen shape first:
+//   FP32 64 x 64      16x4 3.04, 16x8 3.4, 32x4 3.4, 64x8 4.7; one-level 4.99
+//        256 x 128    32x4 3.5, 32x8 on 576 threads 3.8, 16x4 3.95; one-level 5.31
+//        256 x 256    32x8 on 576 threads 3.9, 32x4 4.4, 64x8 5.0; one-level 5.74
+//        256 x 512    32x16 5.03, 64x8 5.2, 32x8 5.5
+//        256 x 1024   64x16 6.7, 64x8 6.7, 32x16 6.9
+//        1024 x 512   32x16 12.8, 64x8 13.2, 64x16 13.5; 1024 x 1024 23.1, 23.7, 26.5
+//        4096 x 4096  64x8 364, 32x8 375, 32x16 395 (streamed from HBM)
+//   FP64 64 x 64      16x4 3.67, 32x4 4.3, 64x8 6.9; one-level 9.07
+//        200 x 100    32x4 4.3, 16x4 4.3, 32x8 5.6; one-level 14.5
+//        300 x 300    32x16 7.2, 32x8 7.35, 64x8 7.3
+//        1000 x 500   32x8 24.0, 32x16 26.5, 64x8 27.6; 1999 x 2203 228, 312, 294
+// The 32x8 tiles of FP64 (80 KB of LDS) run two workgroups of 256 threads per
+// CU; of one node per thread (576 threads) they serve single-round lattices.
+// S2_NONE: no tile shape has as many stamps as tiles (FP64, one row).
+enum Step2Shape { S2_NONE, S2_16x4, S2_32x4, S2_32x8_WIDE, S2_32x16, S2_64x16, S2_64x8, S2_32x8 };
+inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool cached) {
+    auto tiles = [&](int tw, int ty) { return (long long)((nx + tw - 1) / tw) * ((ny + ty - 1) / ty); };
+    auto one_round = [&](int tw, int ty) { return tiles(tw, ty) <= 256 && stamp_share_ok(nx, ny, tw, ty); };
+    if (one_round(16, 4)) return S2_16x4;
+    if (one_round(32, 4)) return S2_32x4;
+    if (one_round(32, 8)) return S2_32x8_WIDE;
+    if (one_round(32, 16)) return S2_32x16;
+    if (esz == 8) return stamp_share_ok(nx, ny, 32, 8) ? S2_32x8 : S2_NONE;
+    if (one_round(64, 16)) return S2_64x16;
+    return cached && stamp_share_ok(nx, ny, 32, 16) ? S2_32x16 : S2_64x8;
+}
+
 // the Allen-Cahn step (either gradient scheme, not the corrected model) on a
-// lattice of at least one tile per CU whose copy fits 32-bit offsets: two
-// levels per launch
-bool two_level_path(const Layout& L, int nx, int ny, int pf, int model, int grad);
+// lattice whose copy fits 32-bit offsets: lbm_step folds two levels into a
+// launch (not with LBM_TWO_LEVEL=0 in the environment)
+bool two_level_step(const Layout& L, int nx, int ny, int pf, int model);
+// the same with the size rule of the 64-wide tiles: what lbm_levels_per_launch
+// reports, and the rule of the batches
+bool two_level_path(const Layout& L, int nx, int ny, int pf, int model);
 template <typename T>
 hipError_t launch_moments(const KParams<T>& P, const char* state, const Layout& L, T* phi, T* u, T* p,
                           hipStream_t s);

@@ -387,35 +387,43 @@ static void launch_tile(const KParams<T>& P, char* state, const Layout& L, hipSt
 }
 
 // Two levels per launch for the Allen-Cahn step with either gradient scheme
-// (stencils or Eq. local; present or original model; lbm_step2.hip) on
-// lattices of at least one 64 x 8 tile per CU whose copy fits 32-bit offsets.
-// Measured on MI355X, FP32, per level: 256 x 1024 (cache-resident) 7.2 us
-// against 9.0 one-level, 1024 x 512 14.4 against 16.1, 4096 x 4096 (streamed
-// from HBM, which the two-level launch crosses once per two levels) 378 against
-// 521; FP64 4096 x 4096 974 against 985.  Below the size rule, where every CU
-// runs at most one short tile, the longer chain of the two-level tile costs
-// more than the launch it saves (256 x 128: 5.1 against 4.8 us, 64 x 8: 4.9
-// against 4.7).  The environment variable LBM_TWO_LEVEL, read at every call,
-// overrides the size rule: "0" never, "1" on every eligible state whatever its
-// size.  The compile-time LBM_TWO_LEVEL=0 removes the path.
+// (stencils or Eq. local; present or original model; lbm_step2.hip) on lattices
+// whose copy fits 32-bit offsets, with tiles by size (step2_shape): one-level
+// launches are slower on every lattice measured (64 x 64 FP32 4.99 against 3.04
+// us per level, FP64 9.07 against 3.67; 4096 x 4096 523 against 364).  The
+// environment variable LBM_TWO_LEVEL, read at every call, turns it off ("0").
+// lbm_levels_per_launch reports the rule of the 64-wide tiles, at least 256
+// 64 x 8 tiles (every eligible state with LBM_TWO_LEVEL "1"): below it a launch
+// is bound by its own latency, not by the bytes of a level.  The compile-time
+// LBM_TWO_LEVEL=0 removes the path.
 #ifndef LBM_TWO_LEVEL
 #define LBM_TWO_LEVEL 1
 #endif
 
-bool two_level_path(const Layout& L, int nx, int ny, int pf, int model, int grad) {
-    if (!LBM_TWO_LEVEL || pf != 0 || model == 2 || L.buf_bytes >= (size_t(1) << 32)) return false;
+static char two_level_env() {   // '0', '1' or, unset or anything else, 0
     const char* e = getenv("LBM_TWO_LEVEL");
-    if (e && e[0] == '0' && e[1] == 0) return false;
-    if (e && e[0] == '1' && e[1] == 0) return true;
+    return e && (e[0] == '0' || e[0] == '1') && e[1] == 0 ? e[0] : 0;
+}
+
+static bool two_level_eligible(const Layout& L, int pf, int model) {
+    return LBM_TWO_LEVEL && pf == 0 && model != 2 && L.buf_bytes < (size_t(1) << 32) && two_level_env() != '0';
+}
+
+bool two_level_step(const Layout& L, int nx, int ny, int pf, int model) {
+    return two_level_eligible(L, pf, model) && step2_shape(nx, ny, L.esz, cached_state(L)) != S2_NONE;
+}
+
+bool two_level_path(const Layout& L, int nx, int ny, int pf, int model) {
+    if (!two_level_eligible(L, pf, model)) return false;
     const long long tiles8 = (long long)((nx + TX - 1) / TX) * ((ny + 7) / 8);
-    return tiles8 >= 256;
+    return two_level_env() == '1' || tiles8 >= 256;
 }
 
 template <typename T>
 hipError_t launch_step(const KParams<T>& P, char* state, const Layout& L, int64_t nsteps, hipStream_t s,
                        int ty, int by, int& copy) {
     constexpr int T16 = sizeof(T) == 8 ? 8 : 16;   // FP64 tiles stop at 8 rows
-    if (two_level_path(L, P.nx, P.ny, P.pf, P.model, P.grad))
+    if (two_level_step(L, P.nx, P.ny, P.pf, P.model))
         for (; nsteps >= 2; nsteps -= 2) {
             launch_step2<T>(P, state, L, s);
             copy ^= 1;

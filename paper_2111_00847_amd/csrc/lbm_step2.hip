@@ -1,12 +1,11 @@
-// lbm_step2.hip -- two time levels of the Allen-Cahn step (stencil gradients)
-// per launch.
+// lbm_step2.hip -- two time levels of the Allen-Cahn step (either gradient
+// scheme) per launch.
 //
-// On states that the last-level cache holds, a one-level launch is bound by
-// its own latency (the load, window, collide, store chain of every tile, and
-// the launch itself) more than by bytes; on larger states it is bound by HBM,
-// which it crosses once per level.  A two-level launch pays the chain once and
-// crosses HBM once for two levels: a tile of 64 x TY nodes advances from level
-// n to n + 2 by
+// On small lattices a one-level launch is bound by its own latency (the load,
+// window, collide, store chain of a tile, and the launch itself) more than by
+// bytes; on larger ones it is bound by HBM, which it crosses once per level.  A
+// two-level launch pays the chain once and crosses HBM once for two levels: a
+// tile of TW x TY nodes advances from level n to n + 2 by
 //   A. computing level n + 1 (the step of level n) on the tile and a two-node
 //      ring around it: the populations of that region are pulled from the
 //      state, phi of level n on a three-node ring is summed into an LDS
@@ -19,10 +18,15 @@
 // what a one-level step would load back from the copy written by A (the FP32
 // rest population included: it is kept in the stored encoding), so two levels
 // of this launch equal two one-level launches bit for bit.  The ring costs
-// recomputation (the region of A is (64 + 4)(TY + 4) nodes) and L2 reads of
+// recomputation (the region of A is (TW + 4)(TY + 4) nodes) and L2 reads of
 // the neighbouring tiles' rows, not HBM traffic beyond those rows: a launch
 // reads the state once and writes it once for two levels.  Stores bypass the
 // caches (non-temporal) on states larger than the last-level cache.
+//
+// Where the time of a launch goes (wave clocks, 256 x 1024 FP32, 64 x 16 tiles, one
+// per CU, before the window's ring was read with the region and the stores wrote
+// through): 4.0 us until the loads are in, 3.9 A, 1.9 B and its stores, and 3.5
+// between launches.
 //
 // A launch writes level n + 2 into the other copy (the level stamps carry the
 // copy, lbm_common.hpp).
@@ -32,78 +36,49 @@
 namespace lbm {
 
 // Two levels of one tile per workgroup, tiles dealt to the XCDs (xcd_tile).
-template <typename T, int TY, int NBY, bool STD, bool NTS>
-__global__ __launch_bounds__(TX* NBY) void k_step2(KParams<T> P, char* state, size_t off0, size_t off1,
-                                                   size_t off_stamp, int ntx, int nty) {
-    __shared__ Step2Lds<T, TY> L;
-    int xt, yt;
-    xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_tile<T, TY, NBY, STD, NTS>(P, state, off0, off1, off_stamp, xt, yt, L);
-}
-
-// The same for the local gradient scheme (Eq. local; the general collision,
+// P is the kernel's first argument: the body reads it from the argument
+// segment.  LOCAL: the local gradient scheme (Eq. local; the general collision,
 // as the one-level kernel runs it).
-template <typename T, int TY, int NBY, bool NTS>
-__global__ __launch_bounds__(TX* NBY) void k_step2_local(KParams<T> P, char* state, size_t off0, size_t off1,
-                                                         size_t off_stamp, int ntx, int nty) {
-    __shared__ Step2LdsLocal<T, TY> L;
+template <typename T, int TW, int TY, int NT, bool STD, bool NTS, bool LOCAL>
+__global__ __launch_bounds__(NT) void k_step2(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stamp,
+                                              int ntx, int nty, StampShare sh) {
+    __shared__ Step2Lds<T, TW, TY, LOCAL> L;
     int xt, yt;
     xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_local_tile<T, TY, NBY, NTS>(P, state, off0, off1, off_stamp, xt, yt, L);
+    step2_body<T, TW, TY, NT, STD, NTS, false, LOCAL>(
+        (ParamsPtr<T>)__builtin_amdgcn_kernarg_segment_ptr(),
+        StateTile{state, off0, off1, off_stamp, sh, (int)blockIdx.x, xt, yt, 0}, L);
 }
 
-template <typename T, int TY, int NBY>
-static void launch_step2_local(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
-    const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
-    if (cached_state(L))
-        k_step2_local<T, TY, NBY, false><<<ntx * nty, dim3(TX, NBY), 0, s>>>(P, state, L.off_buf[0], L.off_buf[1],
-                                                                             L.off_stamp, ntx, nty);
-    else
-        k_step2_local<T, TY, NBY, true><<<ntx * nty, dim3(TX, NBY), 0, s>>>(P, state, L.off_buf[0], L.off_buf[1],
-                                                                            L.off_stamp, ntx, nty);
-}
-
-template <typename T, int TY, int NBY, bool STD>
-static void launch_step2_std(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
-    const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
+template <typename T, int TW, int TY, int NT>
+static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
+    const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
+    const StampShare sh = stamp_share((long long)L.nstamp, (long long)ntx * nty);
+    const dim3 grd(ntx * nty), blk(TX, NT / TX);
+    auto go = [&](auto kernel) {
+        kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh);
+    };
     // the one-level step's store policy: ordinary stores while both copies fit the cache
-    if (cached_state(L))
-        k_step2<T, TY, NBY, STD, false><<<ntx * nty, dim3(TX, NBY), 0, s>>>(P, state, L.off_buf[0], L.off_buf[1],
-                                                                            L.off_stamp, ntx, nty);
-    else
-        k_step2<T, TY, NBY, STD, true><<<ntx * nty, dim3(TX, NBY), 0, s>>>(P, state, L.off_buf[0], L.off_buf[1],
-                                                                           L.off_stamp, ntx, nty);
+    const bool cached = cached_state(L);
+    if (P.grad == 1) cached ? go(k_step2<T, TW, TY, NT, false, false, true>) : go(k_step2<T, TW, TY, NT, false, true, true>);
+    else if (P.rates_std) cached ? go(k_step2<T, TW, TY, NT, true, false, false>) : go(k_step2<T, TW, TY, NT, true, true, false>);
+    else cached ? go(k_step2<T, TW, TY, NT, false, false, false>) : go(k_step2<T, TW, TY, NT, false, true, false>);
 }
 
-template <typename T, int TY, int NBY>
-static void launch_step2_ty(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
-    if (P.grad == 1) launch_step2_local<T, TY, NBY>(P, state, L, s);
-    else if (P.rates_std) launch_step2_std<T, TY, NBY, true>(P, state, L, s);
-    else launch_step2_std<T, TY, NBY, false>(P, state, L, s);
-}
-
-// Tile rows of the two-level launch.  8-row tiles (68 KB of LDS in FP32, 136 KB
-// in FP64) run two workgroups of 512 threads per CU (FP32); 16-row FP32 tiles
-// (117 KB) one of 1024 threads, with 1.33 region nodes per tile node against
-// 1.59.  Measured on MI355X (FP32): 16 rows when they fill the 256 CUs in one
-// round and 8 rows would need two workgroups per CU (256 x 1024: 7.77 against
-// 8.12 us per level); 8 rows otherwise (1024 x 512: 15.6 against 16.2 us).
-// LBM_STEP2_TY forces 4, 8 or 16 (FP32).
-#ifndef LBM_STEP2_TY
-#define LBM_STEP2_TY 0
-#endif
-
+// The launch's tiles (step2_shape).
 template <typename T>
 void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
-    const long long ntx = (P.nx + TX - 1) / TX;
-    const long long t8 = ntx * ((P.ny + 7) / 8), t16 = ntx * ((P.ny + 15) / 16);
-    const bool rows16 = LBM_STEP2_TY == 16 || (LBM_STEP2_TY == 0 && t16 <= 256 && t8 > 256);
-    if constexpr (LBM_STEP2_TY == 4) launch_step2_ty<T, 4, 4>(P, state, L, s);
-    else if constexpr (sizeof(T) == 4) {
-        if (rows16) launch_step2_ty<T, 16, 16>(P, state, L, s);
-        else launch_step2_ty<T, 8, 8>(P, state, L, s);
-    } else {
-        launch_step2_ty<T, 8, 8>(P, state, L, s);
+    switch (step2_shape(P.nx, P.ny, sizeof(T), cached_state(L))) {
+        case S2_16x4: launch_step2_shape<T, 16, 4, 256>(P, state, L, s); break;
+        case S2_32x4: launch_step2_shape<T, 32, 4, 384>(P, state, L, s); break;
+        case S2_32x8_WIDE: launch_step2_shape<T, 32, 8, 576>(P, state, L, s); break;
+        case S2_32x16: launch_step2_shape<T, 32, 16, 512>(P, state, L, s); break;
+        case S2_64x16:
+            if constexpr (sizeof(T) == 4) launch_step2_shape<T, 64, 16, 1024>(P, state, L, s);
+            break;
+        default:
+            if constexpr (sizeof(T) == 8) launch_step2_shape<T, 32, 8, 256>(P, state, L, s);
+            else launch_step2_shape<T, 64, 8, 512>(P, state, L, s);
     }
 }
 

@@ -1,0 +1,48 @@
+"""The tile shapes of the two-level launch, each where the size rule takes it.
+
+lbm_step advances two levels per launch with the tile shape its size rule picks
+(16 x 4 to 64 x 16 nodes).  Every shape runs here on a lattice of its own range,
+ragged in both directions where the shape allows it, from level 0 and on: six
+levels by one call equal six one-level launches (LBM_TWO_LEVEL=0) bit for bit.
+The lattice of one row has fewer level stamps than tiles in FP64 and keeps
+one-level launches.
+"""
+import os
+
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = {   # size -> the shape the rule takes there (FP32 / FP64)
+    (125, 60): "16x4", (64, 41): "32x4 (too few stamps for 16x4)", (250, 126): "32x4", (250, 250): "32x8, one round",
+    (250, 500): "32x16, one round", (250, 1020): "64x16 / 32x8", (1020, 500): "32x16 cached / 32x8",
+    (2050, 1100): "64x8 streamed / 32x8", (17000, 1): "64x8 / one level",
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("size", list(SHAPES), ids=[f"{a}x{b}" for a, b in SHAPES])
+@pytest.mark.parametrize("grad", ["stencil", "local"])
+def test_shape_equals_one_level_launches(size, dtype, grad):
+    from paper_2111_00847_amd.sim import Sim
+    nx, ny = size
+    case = W.Case(nx=nx, ny=ny, wall_x=nx % 4 == 2, wall_y=ny > 1 and ny % 4 != 1, rhoA=20.0, nuA=0.05, nuB=0.2,
+                  sigma=0.01, M=0.05, gravity=(0.0, -1e-5), rho_ref=3.0, dtype=dtype, theta=(1.2, 1.9, 0.7, 2.4),
+                  grad_scheme=grad)
+    phi0, u0, p0 = W.random_state_fields(case, seed=nx + ny)
+    a, b = Sim(case).init(phi0, u0, p0), Sim(case).init(phi0, u0, p0)
+    print(f"{nx}x{ny} {dtype} {grad}: {SHAPES[size]}", flush=True)
+    a.step(6)
+    os.environ["LBM_TWO_LEVEL"] = "0"
+    try:
+        b.step(6)
+    finally:
+        os.environ.pop("LBM_TWO_LEVEL", None)
+    sa, sb = a.export_state(), b.export_state()
+    assert sa["step"] == sb["step"] == 6
+    for k in ("f", "g", "hist"):
+        assert torch.equal(sa[k], sb[k]), (k, float((sa[k] - sb[k]).abs().max()))
