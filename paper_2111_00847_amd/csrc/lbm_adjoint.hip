@@ -63,8 +63,6 @@ static int validate_ac(const lbm_params* p) {
 
 constexpr size_t ADJ_HDR = 256;
 constexpr size_t TAPE_HDR = 256;
-constexpr int ATY = 16;   // tiles of kernel A: 64 x 16, one node per thread of 64 x ABY
-constexpr int ABY = 16;
 constexpr int BTY = BY;   // tiles of kernel B: 64 x 4, one node per thread
 
 struct TapeHeader {
@@ -102,6 +100,22 @@ static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
 static int ghost_blocks(const lbm_params* p);
 
+// Tiles of kernel A, one node per thread: 32 x 4 (two waves) while they are at
+// most two to a CU, where the latency of a tile sets the kernel's duration, else
+// 64 x 4.  Workgroups of at most 256 threads also leave the FP64 body its 208
+// registers (64 x 16 tiles of 1024 threads had 128 and spilled).  Measured on
+// MI355X, us per adjoint step (kernels A, G and B), against 64 x 16:
+//   96 x 48 FP64 22.0 / 52.9, FP32 20.3 / 25.3; 256 x 128 FP64 25.4 / 60.1
+//   1024 x 512 FP64 89.1 (32 x 4 90.2, 64 x 8 90.2) / 170.6, FP32 48.8 (53.0, 49.8) / 49.5
+//   2048 x 1024 FP32 160 (172, 163) / 177
+struct AdjTile {
+    int w, h;
+};
+static AdjTile adj_tile(int nx, int ny) {
+    const long long t = (long long)((nx + 31) / 32) * ((ny + 3) / 4);
+    return t <= 512 ? AdjTile{32, 4} : AdjTile{64, 4};
+}
+
 AdjLayout adj_layout_of(const lbm_params* p) {
     Layout L = layout_of(p);
     AdjLayout A;
@@ -114,7 +128,8 @@ AdjLayout adj_layout_of(const lbm_params* p) {
     A.off_edge = A.off_scr + (size_t)S_COUNT * L.plane * L.esz;
     A.emax = ((long long)(p->nx > p->ny ? p->nx : p->ny) + 63) / 64 * 64;
     A.off_part = al256(A.off_edge + (size_t)16 * A.emax * L.esz);
-    A.ntA = ((p->nx + TX - 1) / TX) * ((p->ny + ATY - 1) / ATY);
+    const AdjTile t = adj_tile(p->nx, p->ny);
+    A.ntA = ((p->nx + t.w - 1) / t.w) * ((p->ny + t.h - 1) / t.h);
     A.ntB = ((p->nx + TX - 1) / TX) * ((p->ny + BTY - 1) / BTY);
     A.nB = ghost_blocks(p);   // workgroups of kernel G
     A.total = al256(A.off_part + (size_t)(2 * A.ntA + 4 * A.nB) * sizeof(double));
@@ -225,47 +240,26 @@ __global__ __launch_bounds__(NT) void k_tape_step2(KParams<T> P, char* tape, siz
 }
 
 // ---------------------------------------------------------------- adjoint step, kernel A
-// Adjoint of post-collision population i of node (x, y): the population
-// streams to (x, y) + c_i, or back to (x, y) as opp(i) through a wall.
-// planes: the adjoint copy of level n + 1; returns fd + phib of the receiver.
-// Adjoints of post-collision f_i and g_i of node (x, y), read where they
-// stream to (fd + phib of the receiver; phib from the LDS window `sb`, whose
-// position (wx, wy) is the node's own).
-template <typename T, typename OFF>
-__device__ __forceinline__ void push_read(const char* cp, OFF pl, const KParams<T>& P, int i, int x, int y,
-                                          const T (*sb)[TX + 3], int wx, int wy, T& fo, T& go) {
-    constexpr OFF ES = sizeof(T);
-    int tx = x + cx(i), ty = y + cy(i);
-    bool bb = false;
-    if (tx < 0 || tx >= P.nx) {
-        if (P.wall_x) bb = true;
-        else tx = tx < 0 ? tx + P.nx : tx - P.nx;
-    }
-    if (ty < 0 || ty >= P.ny) {
-        if (P.wall_y) bb = true;
-        else ty = ty < 0 ? ty + P.ny : ty - P.ny;
-    }
-    const OFF k = bb ? (OFF)y * (OFF)P.nx + (OFF)x : (OFF)ty * (OFF)P.nx + (OFF)tx;
-    const OFF d = (OFF)(bb ? opp(i) : i);
-    fo = ld<T>(cp, (d * pl + k) * ES) + (bb ? sb[wy][wx] : sb[wy + cy(i)][wx + cx(i)]);
-    go = ld<T>(cp, ((9 + d) * pl + k) * ES);
-}
-
-// One 64 x ATY tile per workgroup of 64 x ABY threads, ATY / ABY nodes per
-// thread.  Every thread pulls its nodes' populations from the tape slot once
-// (their phi goes into the LDS window), spare threads pull the window's ring,
-// and the node update is recomputed from the registers.  OFF: byte offsets
-// within a tape slot and within the adjoint buffer.
-template <typename T, typename OFF>
-__global__ __launch_bounds__(TX* ABY) void k_adj_local(KParams<T> P, const char* tape, size_t slot, int j,
+// One TW x TY tile per workgroup, one node per thread.  Every thread pulls its
+// node's populations from the tape slot once (their phi goes into the LDS
+// window) and reads the adjoint of its post-collision populations where they
+// stream to (the receiver's fd + phib, phib from an LDS window); all threads
+// fill the windows' ring, and the node update is recomputed from the registers.
+// OFF: byte offsets within a tape slot and within an adjoint copy.  EARLY: the
+// adjoints are loaded with the node's populations, one round trip fewer (0.8 us
+// of a step at 96 x 48); later, after the window barrier, once the tiles run in
+// many rounds (1024 x 512 FP32 48.8 against 50.0 us, 2048 x 1024 160 against 162.5).
+// Stores are ordinary: written through the L2 they cost 1-2% here.
+template <typename T, typename OFF, int TW, int TY, bool EARLY>
+__global__ __launch_bounds__(TW* TY) void k_adj_local(KParams<T> P, const char* tape, size_t slot, int j,
                                                       AdjView<T> V) {
-    constexpr int R = ATY / ABY;
-    constexpr int WX = TX + 2, WY = ATY + 2;
+    constexpr int NT = TW * TY, WX = TW + 2, WY = TY + 2, PITCH = TW + 3;
     constexpr OFF ES = sizeof(T);
-    __shared__ T sphi[ATY + 2][TX + 3];
-    __shared__ T sphp[ATY + 2][TX + 3];
-    __shared__ T sphib[ATY + 2][TX + 3];   // phib of level n + 1 on the tile and its ring
-    __shared__ double red[2][ABY];
+    static_assert(NT % 64 == 0, "whole waves");
+    __shared__ T sphi[WY][PITCH];
+    __shared__ T sphp[WY][PITCH];
+    __shared__ T sphib[WY][PITCH];   // phib of level n + 1 on the tile and its ring
+    __shared__ double red[2][NT / 64];
     // The tape must hold slot j and have been recorded for this lattice and
     // dtype; otherwise nothing of the tape beyond its header is read, the
     // status records why, and the later kernel of the step (which exits on a
@@ -275,120 +269,137 @@ __global__ __launch_bounds__(TX* ABY) void k_adj_local(KParams<T> P, const char*
                          TH->dtype == (sizeof(T) == 8 ? LBM_F64 : LBM_F32);
     const int64_t n = TH->n0 + j;
     AdjHeader* H = V.hdr();
-    const int tid = threadIdx.y * TX + threadIdx.x;
+    const int tid = threadIdx.x;
     if (!tape_ok || H->status != 0 || H->level != n + 1) {
         if (blockIdx.x == 0 && tid == 0 && H->status == 0) H->status = tape_ok ? 1 : 3;
         return;
     }
     const bool first = n == 0;
-    const char* src = tape + TAPE_HDR + (size_t)j * slot;
-    const OFF pl = (OFF)P.plane;
-    const OFF bF = pl * ES, bG = bF + 8 * pl * ES, bH = bG + 9 * pl * ES;
-    const int ntx = (P.nx + TX - 1) / TX;
+    const OFF plB = (OFF)P.plane * ES;
+    const int ntx = (P.nx + TW - 1) / TW;
     int xt, yt;   // tiles dealt to the XCDs as the step deals them: halo rows stay in one L2
     xcd_tile(blockIdx.x, ntx, V.ntA / ntx, xt, yt);
-    const int x0 = xt * TX, y0 = yt * ATY;
-    const int lx = threadIdx.x;
-    const int x = x0 + lx;
+    const int x0 = xt * TW, y0 = yt * TY;
+    const int ly = tid / TW, lx = tid - ly * TW;
+    const int x = x0 + lx, y = y0 + ly;
     const int ci = (int)((n + 1) & 1), co = (int)(n & 1);
-    const char* cin = reinterpret_cast<const char*>(V.copy[ci]);
-    const OFF bPB = (OFF)P_PHIB * pl * ES;
+    const CopyAddr<OFF> src(tape + TAPE_HDR + (size_t)j * slot, 21 * plB);
+    const CopyAddr<OFF> cin(reinterpret_cast<const char*>(V.copy[ci]), ADJ_PLANES * plB);
+    const bool inner = x0 >= 2 && x0 + TW + 2 <= P.nx && y0 >= 2 && y0 + TY + 2 <= P.ny;
+    const bool own = inner || (x < P.nx && y < P.ny);
 
-    // own nodes: populations, history, phi into the window
-    T f[R][9], g[R][9], up[R], vp[R];
-    double phid[R];
+    // own node: populations, history, phi and phib into the windows, and the
+    // adjoints where its populations stream to (their phib is added below)
+    T f[9], g[9], up = T(0), vp = T(0), fo[9], go[9], hphi = T(0), hu = T(0), hv = T(0);
+    double phid = 0.0;
+    auto load_adjoints = [&]() {
+        OFF to[9];
+        int xi, yi;
+        neighbour_offsets<T, OFF, 1>(P, inner, x, y, to, xi, yi);
+        fo[0] = cin.template ld<T>(to[0], 0);
+        go[0] = cin.template ld<T>(to[0], 9 * plB);
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int ly = threadIdx.y + r * ABY, y = y0 + ly;
-        phid[r] = 0.0;
-        up[r] = vp[r] = T(0);
-        if (x >= P.nx || y >= P.ny) continue;
-        double f0;
-        const OFF k = pull_fg_at<T, OFF>(P, src, bF, bG, bH, pl, x, y, f[r], f0, g[r]);
-        f[r][0] = (T)f0;
-        phid[r] = f0 + moving_sum_d(f[r]);
-        const T hp = ld<T>(src, bH + k * ES);
-        up[r] = ld<T>(src, bH + (pl + k) * ES);
-        vp[r] = ld<T>(src, bH + (2 * pl + k) * ES);
-        sphi[ly + 1][lx + 1] = (T)phid[r];
+        for (int i = 1; i < Q; i++) {
+            fo[i] = cin.template ld<T>(to[i], pair_plane(i) * plB);
+            go[i] = cin.template ld<T>(to[i], (9 + pair_plane(i)) * plB);
+        }
+        hphi = cin.template ld<T>(to[0], 18 * plB);
+        hu = cin.template ld<T>(to[0], 19 * plB);
+        hv = cin.template ld<T>(to[0], 20 * plB);
+    };
+    if (own) {
+        OFF off[9];
+        int xi, yi;
+        neighbour_offsets<T, OFF, -1>(P, inner, x, y, off, xi, yi);
+        const T f0s = src.template ld<T>(off[0], 0), hp = src.template ld<T>(off[0], 18 * plB);
+#pragma unroll
+        for (int i = 1; i < Q; i++) f[i] = src.template ld<T>(off[i], pair_plane(i) * plB);
+        const T pb = cin.template ld<T>(off[0], P_PHIB * plB);
+        g[0] = src.template ld<T>(off[0], 9 * plB);
+#pragma unroll
+        for (int i = 1; i < Q; i++) g[i] = src.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
+        up = src.template ld<T>(off[0], 19 * plB);
+        vp = src.template ld<T>(off[0], 20 * plB);
+        if (EARLY) load_adjoints();
+        const double f0 = rest_decode(f0s, hp, P.rest_w);
+        f[0] = (T)f0;
+        phid = f0 + moving_sum_d(f);
+        sphi[ly + 1][lx + 1] = (T)phid;
         if (!first) sphp[ly + 1][lx + 1] = hp;
-        sphib[ly + 1][lx + 1] = ld<T>(cin, bPB + k * ES);
+        sphib[ly + 1][lx + 1] = pb;
     }
     // the ring of the window, and positions of a ragged tile beyond the
     // lattice that a periodic axis wraps onto nodes
     auto fill = [&](int wx, int wy) {
-        const int gx = region_node(x0 - 1 + wx, P.nx, P.wall_x), gy = region_node(y0 - 1 + wy, P.ny, P.wall_y);
-        if (gx < 0 || gy < 0) return;
+        OFF off[9];
+        int xi, yi;
+        if (!neighbour_offsets<T, OFF, -1>(P, inner, x0 - 1 + wx, y0 - 1 + wy, off, xi, yi)) return;
         T fw[9];
-        double fw0;
-        const OFF k = pull_f_at<T, OFF>(P, src, bF, bH, pl, gx, gy, fw, fw0);
-        sphi[wy][wx] = (T)(fw0 + moving_sum_d(fw));
-        if (!first) sphp[wy][wx] = ld<T>(src, bH + k * ES);
-        sphib[wy][wx] = ld<T>(cin, bPB + k * ES);
+        const T fw0 = src.template ld<T>(off[0], 0), hw = src.template ld<T>(off[0], 18 * plB);
+#pragma unroll
+        for (int i = 1; i < Q; i++) fw[i] = src.template ld<T>(off[i], pair_plane(i) * plB);
+        sphib[wy][wx] = cin.template ld<T>(off[0], P_PHIB * plB);
+        sphi[wy][wx] = (T)(rest_decode(fw0, hw, P.rest_w) + moving_sum_d(fw));
+        if (!first) sphp[wy][wx] = hw;
     };
-    for (int idx = tid; idx < 2 * WX + 2 * ATY; idx += TX * ABY) {
-        if (idx < 2 * WX) fill(idx % WX, idx < WX ? 0 : WY - 1);
-        else fill(idx < 2 * WX + ATY ? 0 : WX - 1, 1 + (idx - 2 * WX) % ATY);
+    for (int idx = tid; idx < 2 * WX + 2 * TY; idx += NT) {
+        if (idx < 2 * WX) fill(idx < WX ? idx : idx - WX, idx < WX ? 0 : WY - 1);
+        else fill(idx < 2 * WX + TY ? 0 : WX - 1, 1 + idx - 2 * WX - (idx < 2 * WX + TY ? 0 : TY));
     }
-    if (x0 + TX > P.nx || y0 + ATY > P.ny)
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int ly = threadIdx.y + r * ABY;
-            if (x >= P.nx || y0 + ly >= P.ny) fill(lx + 1, ly + 1);
-        }
+    if (!own) fill(lx + 1, ly + 1);
     __syncthreads();
-    wall_ghosts<T, ATY, ABY>(P, !first, x0, y0, sphi, sphp);
+    if (!inner) ghosts_h<T, WX, WY, 1, NT, PITCH>(P, !first, x0, y0, sphi, sphp, tid);
 
-    char* cout = reinterpret_cast<char*>(V.copy[co]);
-    char* scr = reinterpret_cast<char*>(V.scr);
     double gsum_x = 0.0, gsum_y = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int ly = threadIdx.y + r * ABY, y = y0 + ly;
-        if (x >= P.nx || y >= P.ny) continue;
-        const OFF k = (OFF)y * (OFF)P.nx + (OFF)x;
+    if (own) {
+        if (!EARLY) load_adjoints();
         T gx, gy, lap, gxp = T(0), gyp = T(0), lp, php = T(0);
-        win_stencil<T, ATY>(sphi, lx + 1, ly + 1, gx, gy, lap);
+        win_stencil_at(sphi, lx + 1, ly + 1, gx, gy, lap);
         if (!first) {
-            win_stencil<T, ATY>(sphp, lx + 1, ly + 1, gxp, gyp, lp);
+            win_stencil_at(sphp, lx + 1, ly + 1, gxp, gyp, lp);
             php = sphp[ly + 1][lx + 1];
+        } else {
+            up = vp = T(0);
         }
-        const T upr = first ? T(0) : up[r], vpr = first ? T(0) : vp[r];
-        const Macro<T> M = macro(P, g[r], sphi[ly + 1][lx + 1], gx, gy, lap, first, php, gxp, gyp, upr, vpr);
-        T fo[9], go[9];
+        const Macro<T> M = macro(P, g, sphi[ly + 1][lx + 1], gx, gy, lap, first, php, gxp, gyp, up, vp);
+        fo[0] += sphib[ly + 1][lx + 1];
 #pragma unroll
-        for (int i = 0; i < Q; i++) push_read<T, OFF>(cin, pl, P, i, x, y, sphib, lx + 1, ly + 1, fo[i], go[i]);
-        const T hphi = ld<T>(cin, (18 * pl + k) * ES), hu = ld<T>(cin, (19 * pl + k) * ES),
-                hv = ld<T>(cin, (20 * pl + k) * ES);
+        for (int i = 1; i < Q; i++) {
+            const bool back = !inner && beyond_wall<1>(P, i, x, y);
+            fo[i] += sphib[ly + 1 + (back ? 0 : cy(i))][lx + 1 + (back ? 0 : cx(i))];
+        }
         NodeAdj<T> A;
-        node_vjp(P, M, f[r], g[r], gx, gy, lap, first, php, gxp, gyp, upr, vpr, fo, go, hphi, hu, hv, A);
+        node_vjp(P, M, f, g, gx, gy, lap, first, php, gxp, gyp, up, vp, fo, go, hphi, hu, hv, A);
+        const CopyAddr<OFF> cout(reinterpret_cast<const char*>(V.copy[co]), ADJ_PLANES * plB);
+        const CopyAddr<OFF> scr(reinterpret_cast<const char*>(V.scr), S_COUNT * plB);
+        const OFF k = ((OFF)y * (OFF)P.nx + (OFF)x) * ES;
 #pragma unroll
         for (int i = 0; i < Q; i++) {
-            *reinterpret_cast<T*>(cout + ((OFF)i * pl + k) * ES) = A.f[i];
-            *reinterpret_cast<T*>(cout + ((OFF)(9 + i) * pl + k) * ES) = A.g[i];
+            cout.template st<ST_PLAIN>(k, i * plB, A.f[i]);
+            cout.template st<ST_PLAIN>(k, (9 + i) * plB, A.g[i]);
         }
-        *reinterpret_cast<T*>(cout + (19 * pl + k) * ES) = first ? T(0) : A.up;
-        *reinterpret_cast<T*>(cout + (20 * pl + k) * ES) = first ? T(0) : A.vp;
+        cout.template st<ST_PLAIN>(k, 19 * plB, first ? T(0) : A.up);
+        cout.template st<ST_PLAIN>(k, 20 * plB, first ? T(0) : A.vp);
         const T sv[7] = {A.phic, A.gx, A.gy, A.lap, A.php, A.gxp, A.gyp};   // S_PHIC .. S_GYP
 #pragma unroll
-        for (int q = 0; q < 7; q++) *reinterpret_cast<T*>(scr + ((OFF)q * pl + k) * ES) = sv[q];
+        for (int q = 0; q < 7; q++) scr.template st<ST_PLAIN>(k, q * plB, sv[q]);
         const bool near_x = P.wall_x && (x < 2 || x >= P.nx - 2);
         const bool near_y = P.wall_y && (y < 2 || y >= P.ny - 2);
-        if (near_x || near_y) *reinterpret_cast<T*>(scr + ((OFF)S_PHI * pl + k) * ES) = M.phi;
-        gsum_x += (double)A.grav_x;
-        gsum_y += (double)A.grav_y;
+        if (near_x || near_y) scr.template st<ST_PLAIN>(k, S_PHI * plB, M.phi);
+        gsum_x = (double)A.grav_x;
+        gsum_y = (double)A.grav_y;
     }
     // per-tile sums of the gravity derivative, accumulated over the steps of a pass
     gsum_x = wave_sum(gsum_x);
     gsum_y = wave_sum(gsum_y);
-    if (lx == 0) {
-        red[0][threadIdx.y] = gsum_x;
-        red[1][threadIdx.y] = gsum_y;
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = gsum_x;
+        red[1][tid >> 6] = gsum_y;
     }
     __syncthreads();
     if (tid == 0) {
         double sx = 0.0, sy = 0.0;
-        for (int w = 0; w < ABY; w++) {
+        for (int w = 0; w < NT / 64; w++) {
             sx += red[0][w];
             sy += red[1][w];
         }
@@ -858,12 +869,18 @@ template <typename T>
 static void launch_adj_step(const KParams<T>& P, const char* tape, size_t slot, int j, const AdjView<T>& V,
                             size_t adj_bytes, hipStream_t s) {
     // 32-bit byte offsets while a tape slot and the adjoint buffer stay below 4 GiB
-    if (slot < (size_t(1) << 32) && adj_bytes < (size_t(1) << 32)) {
-        k_adj_local<T, uint32_t><<<V.ntA, dim3(TX, ABY), 0, s>>>(P, tape, slot, j, V);
+    const bool small = slot < (size_t(1) << 32) && adj_bytes < (size_t(1) << 32);
+    auto a_launch = [&](auto k32, auto k64, int nt) {
+        if (small) k32<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
+        else k64<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
+    };
+    if (adj_tile(P.nx, P.ny).w == 32)
+        a_launch(k_adj_local<T, uint32_t, 32, 4, true>, k_adj_local<T, uint64_t, 32, 4, true>, 128);
+    else a_launch(k_adj_local<T, uint32_t, 64, 4, false>, k_adj_local<T, uint64_t, 64, 4, false>, 256);
+    if (small) {
         if (P.wall_x || P.wall_y) k_adj_ghosts<T, uint32_t><<<V.nB, GHOST_THREADS, 0, s>>>(P, tape, slot, j, V);
         k_adj_gather<T, uint32_t><<<V.ntB, dim3(TX, BY), 0, s>>>(P, tape, j, V);
     } else {
-        k_adj_local<T, uint64_t><<<V.ntA, dim3(TX, ABY), 0, s>>>(P, tape, slot, j, V);
         if (P.wall_x || P.wall_y) k_adj_ghosts<T, uint64_t><<<V.nB, GHOST_THREADS, 0, s>>>(P, tape, slot, j, V);
         k_adj_gather<T, uint64_t><<<V.ntB, dim3(TX, BY), 0, s>>>(P, tape, j, V);
     }

@@ -4,6 +4,7 @@
 // bitwise equality with two one-level steps are described in lbm_step2.hip.
 #pragma once
 
+#include "lbm_addr.hpp"
 #include "lbm_fused.hpp"
 
 namespace lbm {
@@ -14,8 +15,7 @@ namespace lbm {
 // the x-ghosts), on windows of any halo H.  Ends synchronised.
 template <typename T, int WW, int WH, int H, int NT, int PITCH>
 __device__ __forceinline__ void ghosts_h(const KParams<T>& P, bool need_prev, int x0, int y0, T (*a)[PITCH],
-                                         T (*b)[PITCH]) {
-    const int tid = threadIdx.y * TX + threadIdx.x;
+                                         T (*b)[PITCH], int tid) {
     if (P.wall_x) {
         const int wl = H - 1 - x0;          // window column of x = -1
         const int wr = P.nx - x0 + H;       // window column of x = nx
@@ -69,47 +69,6 @@ struct Step2Lds {
     T mxa[LOCAL ? NA : 1], mya[LOCAL ? NA : 1];
 };
 
-// A copy of the state as a buffer resource: an element is addressed by a byte
-// offset per lane plus a uniform plane offset, so that one offset register
-// serves every plane a node is read from or written to and no address is
-// formed on the vector unit.  `bytes`: of the copy (below 4 GiB); offsets
-// beyond it read zero and store nothing.
-struct CopyBuf {
-    __amdgpu_buffer_rsrc_t r;
-};
-__device__ __forceinline__ CopyBuf copy_buf(const char* base, uint32_t bytes) {
-    return CopyBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, bytes, 0x00020000)};
-}
-template <typename T>
-__device__ __forceinline__ T bld(CopyBuf b, uint32_t off, uint32_t plane) {
-    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b.r, off, plane, 0));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b.r, off, plane, 0));
-}
-template <typename T, bool NT>
-__device__ __forceinline__ void bst(CopyBuf b, uint32_t off, uint32_t plane, T v) {
-    constexpr int AUX = NT ? 2 : 16;   // nt; sc1 (write through to memory, the line stays in the L2)
-    if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b.r, off, plane, AUX);
-    else {
-        typedef unsigned u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), b.r, off, plane, AUX);
-    }
-}
-
-// Node of region position p on an axis of n nodes; -1 beyond a wall.  Periodic
-// axes wrap (any number of times: a lattice may be narrower than the region).
-__device__ __forceinline__ int axis_node(int p, int n, bool wall) {
-    if (wall) return (unsigned)p < (unsigned)n ? p : -1;
-    while (p < 0) p += n;
-    while (p >= n) p -= n;
-    return p;
-}
-
-// The plane from whose base a pull of population i is addressed: the lower of i
-// and opp(i) = i +- 2, so that the reflected population (plane opp(i), the
-// node's own offset) lies at a non-negative offset too.
-__host__ __device__ constexpr int pull_plane(int i) { return opp(i) < i ? opp(i) : i; }
-
 // The kernel parameters in constant memory.  params_at() reads the fields that
 // the code after it uses.  In FP64 each phase reads them anew, which keeps them
 // out of scalar registers in between: held from end to end they spilled into
@@ -161,52 +120,10 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
     const int tid = threadIdx.y * TX + threadIdx.x;
     const int x0 = tile.xt * TW, y0 = tile.yt * TY;
     const uint32_t plB = (uint32_t)P.plane * ES;   // bytes of a plane
-    const uint32_t pl2 = 2 * plB, bytes = (LOCAL ? 23 : 21) * plB;
+    const uint32_t bytes = (LOCAL ? 23 : 21) * plB;
     const bool inner = x0 >= 4 && x0 + TW + 4 <= P.nx && y0 >= 4 && y0 + TY + 4 <= P.ny;
     const bool walls = P.wall_x || P.wall_y;
 
-    // Byte offsets from which the populations of region position (px, py) are
-    // pulled (off[0]: the node itself; off[i] from the base of plane
-    // pull_plane(i)), its node (xi, yi); false beyond a wall.
-    auto locate = [&](int px, int py, uint32_t (&off)[9], int& xi, int& yi) -> bool {
-        const uint32_t nx = (uint32_t)P.nx;
-        if (inner) {   // no wrap, no wall: nx < 2^24 (ny >= 12 and a copy is below 4 GiB)
-            xi = px;
-            yi = py;
-            const uint32_t k = (__umul24(py - y0 + 4, nx) + (uint32_t)(px - x0 + 4) +
-                                ((uint32_t)(y0 - 4) * nx + (uint32_t)(x0 - 4))) * ES;
-            off[0] = k;
-#pragma unroll
-            for (int i = 1; i < Q; i++)
-                off[i] = k + ((pull_plane(i) == i ? 0u : pl2) - (uint32_t)(cy(i) * P.nx + cx(i)) * ES);
-            return true;
-        }
-        xi = axis_node(px, P.nx, P.wall_x);
-        yi = axis_node(py, P.ny, P.wall_y);
-        if (xi < 0 || yi < 0) return false;
-        uint32_t col[3], row[3];
-        col[1] = (uint32_t)xi;
-        col[0] = xi == 0 ? nx - 1 : (uint32_t)xi - 1;
-        col[2] = xi == P.nx - 1 ? 0u : (uint32_t)xi + 1;
-        row[1] = (uint32_t)yi * nx;
-        row[0] = yi == 0 ? (uint32_t)(P.ny - 1) * nx : row[1] - nx;
-        row[2] = yi == P.ny - 1 ? 0u : row[1] + nx;
-        off[0] = (row[1] + col[1]) * ES;
-#pragma unroll
-        for (int i = 1; i < Q; i++)
-            off[i] = (row[1 - cy(i)] + col[1 - cx(i)]) * ES + (pull_plane(i) == i ? 0u : pl2);
-        if (walls) {   // from beyond a wall: the node's own opp(i)
-            const bool xl = P.wall_x && xi == 0, xh = P.wall_x && xi == P.nx - 1;
-            const bool yl = P.wall_y && yi == 0, yh = P.wall_y && yi == P.ny - 1;
-#pragma unroll
-            for (int i = 1; i < Q; i++) {
-                const bool bb = (cx(i) > 0 ? xl : (cx(i) < 0 ? xh : false)) ||
-                                (cy(i) > 0 ? yl : (cy(i) < 0 ? yh : false));
-                if (bb) off[i] = off[0] + (pull_plane(i) == i ? pl2 : 0u);
-            }
-        }
-        return true;
-    };
     // position s of this thread in A's window; whether it lies in A's region
     auto window_pos = [&](int s, int& wx, int& wy) -> bool {
         const int idx = tid + s * NT;
@@ -222,27 +139,27 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
     T f[S][9], g[S][9], hp[S], hu[S], hv[S], hmx[S], hmy[S], f0s[S];
     bool ok[S];
     int nxi[S], nyi[S];
-    auto load = [&](CopyBuf sb) {
+    auto load = [&](CopyAddr<uint32_t> sb) {
 #pragma unroll
         for (int s = 0; s < S; s++) {
             int wx, wy;
             const bool in = window_pos(s, wx, wy);
             uint32_t off[9];
-            ok[s] = in && locate(x0 - 3 + wx, y0 - 3 + wy, off, nxi[s], nyi[s]);
+            ok[s] = in && neighbour_offsets<T, uint32_t, -1>(P, inner, x0 - 3 + wx, y0 - 3 + wy, off, nxi[s], nyi[s]);
             if (ok[s]) {
-                f0s[s] = bld<T>(sb, off[0], 0);
-                hp[s] = bld<T>(sb, off[0], 18 * plB);
+                f0s[s] = sb.template ld<T>(off[0], 0);
+                hp[s] = sb.template ld<T>(off[0], 18 * plB);
 #pragma unroll
-                for (int i = 1; i < Q; i++) f[s][i] = bld<T>(sb, off[i], pull_plane(i) * plB);
+                for (int i = 1; i < Q; i++) f[s][i] = sb.template ld<T>(off[i], pair_plane(i) * plB);
                 if (in_region(wx, wy)) {
-                    g[s][0] = bld<T>(sb, off[0], 9 * plB);
+                    g[s][0] = sb.template ld<T>(off[0], 9 * plB);
 #pragma unroll
-                    for (int i = 1; i < Q; i++) g[s][i] = bld<T>(sb, off[i], (9 + pull_plane(i)) * plB);
-                    hu[s] = bld<T>(sb, off[0], 19 * plB);
-                    hv[s] = bld<T>(sb, off[0], 20 * plB);
+                    for (int i = 1; i < Q; i++) g[s][i] = sb.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
+                    hu[s] = sb.template ld<T>(off[0], 19 * plB);
+                    hv[s] = sb.template ld<T>(off[0], 20 * plB);
                     if constexpr (LOCAL) {
-                        hmx[s] = bld<T>(sb, off[0], 21 * plB);
-                        hmy[s] = bld<T>(sb, off[0], 22 * plB);
+                        hmx[s] = sb.template ld<T>(off[0], 21 * plB);
+                        hmy[s] = sb.template ld<T>(off[0], 22 * plB);
                     }
                 }
             }
@@ -264,7 +181,7 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
         }
     }
     __syncthreads();
-    if (!inner) ghosts_h<T, WW, WH, 3, NT, WW>(params_at<T>(params), !first && !LOCAL, x0, y0, L.pa, L.pp);
+    if (!inner) ghosts_h<T, WW, WH, 3, NT, WW>(params_at<T>(params), !first && !LOCAL, x0, y0, L.pa, L.pp, tid);
 
     // ---- A: the step of level n on the region
 #pragma unroll
@@ -318,33 +235,27 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
                 L.mya[idx] = M.my;
             }
             if (!inner && walls) {   // what B's pulls from beyond a wall find there
-                const bool xl = P.wall_x && nxi[s] == 0, xh = P.wall_x && nxi[s] == P.nx - 1;
-                const bool yl = P.wall_y && nyi[s] == 0, yh = P.wall_y && nyi[s] == P.ny - 1;
-                if (xl || xh || yl || yh)
 #pragma unroll
-                    for (int i = 1; i < Q; i++) {
-                        const bool bb = (cx(i) > 0 ? xl : (cx(i) < 0 ? xh : false)) ||
-                                        (cy(i) > 0 ? yl : (cy(i) < 0 ? yh : false));
-                        if (bb) {
-                            L.fa[i][idx - cy(i) * AW - cx(i)] = f[s][opp(i)];
-                            L.ga[i][idx - cy(i) * AW - cx(i)] = g[s][opp(i)];
-                        }
+                for (int i = 1; i < Q; i++)
+                    if (beyond_wall<-1>(P, i, nxi[s], nyi[s])) {
+                        L.fa[i][idx - cy(i) * AW - cx(i)] = f[s][opp(i)];
+                        L.ga[i][idx - cy(i) * AW - cx(i)] = g[s][opp(i)];
                     }
             }
             if constexpr (MID) {
                 const int x = x0 + ax - 2, y = y0 + ay - 2;
                 // a node of the tile (not a wrapped position)
                 if (ax >= 2 && ax < AW - 2 && ay >= 2 && ay < AH - 2 && x < P.nx && y < P.ny) {
-                    const CopyBuf mb = copy_buf(tile.mid, bytes);
+                    const CopyAddr<uint32_t> mb(tile.mid, bytes);
                     const uint32_t k = ((uint32_t)y * (uint32_t)P.nx + (uint32_t)x) * ES;
-                    bst<T, true>(mb, k, 0, f0e);
+                    mb.template st<ST_NT>(k, 0, f0e);
 #pragma unroll
-                    for (int i = 1; i < Q; i++) bst<T, true>(mb, k, i * plB, f[s][i]);
+                    for (int i = 1; i < Q; i++) mb.template st<ST_NT>(k, i * plB, f[s][i]);
 #pragma unroll
-                    for (int i = 0; i < Q; i++) bst<T, true>(mb, k, (9 + i) * plB, g[s][i]);
-                    bst<T, true>(mb, k, 18 * plB, M.phi);
-                    bst<T, true>(mb, k, 19 * plB, M.u);
-                    bst<T, true>(mb, k, 20 * plB, M.v);
+                    for (int i = 0; i < Q; i++) mb.template st<ST_NT>(k, (9 + i) * plB, g[s][i]);
+                    mb.template st<ST_NT>(k, 18 * plB, M.phi);
+                    mb.template st<ST_NT>(k, 19 * plB, M.u);
+                    mb.template st<ST_NT>(k, 20 * plB, M.v);
                 }
             }
         }
@@ -387,7 +298,7 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
         }
     }
     __syncthreads();
-    if (!inner) ghosts_h<T, GW, GH, 1, NT, GW + 1>(params_at<T>(params), false, x0, y0, L.pb, L.pb);
+    if (!inner) ghosts_h<T, GW, GH, 1, NT, GW + 1>(params_at<T>(params), false, x0, y0, L.pb, L.pb, tid);
 
     // ---- B: the step of level n + 1 on the tile, stored into the other copy
     if ((NT == TW * TY || tid < TW * TY) && (inner || (x < P.nx && y < P.ny))) {
@@ -413,18 +324,18 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
         const double f0n = collide_f<T, false, STD>(P, M, fb, phb);
         collide_g<T, STD>(P, M, gb);
         const uint32_t k = ((uint32_t)y * (uint32_t)P.nx + (uint32_t)x) * ES;
-        const CopyBuf db = copy_buf(tile.dst(), bytes);
-        bst<T, NTS>(db, k, 0, rest_encode<T>(f0n, M.phi, P.rest_w));
+        const CopyAddr<uint32_t> db(tile.dst(), bytes);
+        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 0, rest_encode<T>(f0n, M.phi, P.rest_w));
 #pragma unroll
-        for (int i = 1; i < Q; i++) bst<T, NTS>(db, k, i * plB, fb[i]);
+        for (int i = 1; i < Q; i++) db.template st<NTS ? ST_NT : ST_THROUGH>(k, i * plB, fb[i]);
 #pragma unroll
-        for (int i = 0; i < Q; i++) bst<T, NTS>(db, k, (9 + i) * plB, gb[i]);
-        bst<T, NTS>(db, k, 18 * plB, M.phi);
-        bst<T, NTS>(db, k, 19 * plB, M.u);
-        bst<T, NTS>(db, k, 20 * plB, M.v);
+        for (int i = 0; i < Q; i++) db.template st<NTS ? ST_NT : ST_THROUGH>(k, (9 + i) * plB, gb[i]);
+        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 18 * plB, M.phi);
+        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 19 * plB, M.u);
+        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 20 * plB, M.v);
         if constexpr (LOCAL) {
-            bst<T, NTS>(db, k, 21 * plB, M.mx);
-            bst<T, NTS>(db, k, 22 * plB, M.my);
+            db.template st<NTS ? ST_NT : ST_THROUGH>(k, 21 * plB, M.mx);
+            db.template st<NTS ? ST_NT : ST_THROUGH>(k, 22 * plB, M.my);
         }
     }
     // every wave read the stamp before the barriers above
@@ -460,7 +371,7 @@ struct StateTile {
     template <typename Load>
     __device__ int64_t load(Load&& loads, uint32_t bytes) {
         sv = stamp()[0];
-        loads(copy_buf(state + (stamp_copy(sv) ? off1 : off0), bytes));
+        loads(CopyAddr<uint32_t>(state + (stamp_copy(sv) ? off1 : off0), bytes));
         return stamp_level(sv);
     }
     __device__ char* dst() const { return state + (stamp_copy(sv) ? off0 : off1); }
@@ -479,7 +390,7 @@ struct TapeTile {
     int xt, yt;
     template <typename Load>
     __device__ int64_t load(Load&& loads, uint32_t bytes) const {
-        loads(copy_buf(src, bytes));
+        loads(CopyAddr<uint32_t>(src, bytes));
         return lev;
     }
     __device__ char* dst() const { return d; }
