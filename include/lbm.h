@@ -145,8 +145,8 @@ int lbm_init(const lbm_params *p, void *state, const void *phi0, const void *u0,
  * rho from the density law of Sec. 2 at phi0, p0 integrates
  * dp/dy = (rho - rho_ref) gravity[1] down every column by the trapezoid rule
  * from the top row, in FP64, then takes the mean out.  phi0, p0: [ny][nx];
- * zero gravity gives p0 = 0.  gravity[0] != 0: LBM_E_UNSUPPORTED.  Runs as one
- * workgroup (an initialisation call, not a per-step one). */
+ * zero gravity gives p0 = 0.  gravity[0] != 0: LBM_E_UNSUPPORTED.  (A p0 that
+ * overlaps phi0 is computed by one workgroup, more slowly.) */
 int lbm_hydrostatic_pressure(const lbm_params *p, const void *phi0, void *p0, void *stream);
 
 /* Advance nsteps >= 0 time steps (Sec. 3): moments, closure, both MRT

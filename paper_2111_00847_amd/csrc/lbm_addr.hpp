@@ -56,6 +56,20 @@ struct CopyAddr<uint64_t> {
     }
 };
 
+// The kernel parameters in constant memory.  params_at() reads the fields that
+// the code after it uses.  In FP64 each phase reads them anew, which keeps them
+// out of scalar registers in between: held from end to end they spilled into
+// vector lanes, 240 of the 2900 vector instructions of the body (1999 x 2203:
+// 237 to 228 us per level).  The FP32 body has registers for them.
+template <typename T>
+using ParamsPtr = const __attribute__((address_space(4))) KParams<T>*;
+
+template <typename T>
+__device__ __forceinline__ KParams<T> params_at(ParamsPtr<T> p) {
+    if constexpr (sizeof(T) == 8) asm volatile("" : "+s"(p));
+    return *(const KParams<T>*)p;
+}
+
 // Node of region position p on an axis of n nodes; -1 beyond a wall.  Periodic
 // axes wrap (any number of times: a lattice may be narrower than the region).
 __device__ __forceinline__ int axis_node(int p, int n, bool wall) {

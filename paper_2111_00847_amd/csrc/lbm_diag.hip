@@ -8,6 +8,7 @@
 // Pass 2 (tile kernel): div m^phiC from the scratch planes, S_m^2 partials.
 // Pass 3 (one workgroup): fixed-order reduction of the partials.  Every
 // reduction has a fixed order, so results are bitwise reproducible.
+#include "lbm_addr.hpp"
 #include "lbm_ch.hpp"
 #include "lbm_kernels.hpp"
 #include "lbm_tile.hpp"
@@ -83,7 +84,7 @@ __device__ __forceinline__ void diag_finish(double* acc, double (*red)[5], doubl
         for (int j = 0; j < 5; j++) partials[b * 8 + j] = acc[j];
 }
 
-template <typename T>
+template <typename T, typename OFF>
 __global__ __launch_bounds__(TX* BY) void k_diag1(KParams<T> P, const char* state, size_t off0,
                                                   size_t off1, size_t off_stamp, T* scr, double* partials) {
     __shared__ T sphi[DTY + 2][TX + 3];
@@ -92,31 +93,80 @@ __global__ __launch_bounds__(TX* BY) void k_diag1(KParams<T> P, const char* stat
     const int64_t sv = *reinterpret_cast<const int64_t*>(state + off_stamp), step = stamp_level(sv);
     const bool first = step == 0;
     const int cur = stamp_copy(sv);
-    const Copy<T> S = copy_at<T>(const_cast<char*>(state) + (cur ? off1 : off0), P.plane);
+    constexpr OFF ES = sizeof(T);
+    const OFF plB = (OFF)P.plane * ES;
+    const CopyAddr<OFF> S(state + (cur ? off1 : off0), (P.grad == 1 ? 23 : 21) * plB);
     const int x0 = blockIdx.x * TX, y0 = blockIdx.y * DTY;
-    fill_window<T, DTY>(P, S, true, x0, y0, sphi, sphp);
+    // own nodes, pulled once for the window and the diagnostics; then the window's
+    // ring (and a ragged tile's positions beyond the lattice, which serve as ring)
+    constexpr int R = DTY / BY, WX = TX + 2;
+    const bool inner = x0 >= 2 && x0 + TX + 2 <= P.nx && y0 >= 2 && y0 + DTY + 2 <= P.ny;
+    T fo[R][9], go[R][9], hu[R], hv[R];
+    double phio[R];
+    // phi of position (px, py) (false beyond a wall), its pulled f, its offsets
+    auto pull_phi = [&](int px, int py, OFF (&off)[9], T* f, double& phid) -> bool {
+        int xi, yi;
+        if (!neighbour_offsets<T, OFF, -1>(P, inner, px, py, off, xi, yi)) return false;
+        const T f0s = S.template ld<T>(off[0], 0), hp = S.template ld<T>(off[0], 18 * plB);
+#pragma unroll
+        for (int i = 1; i < Q; i++) f[i] = S.template ld<T>(off[i], pair_plane(i) * plB);
+        const double f0 = rest_decode(f0s, hp, P.rest_w);
+        f[0] = (T)f0;
+        phid = f0 + moving_sum_d(f);
+        sphi[py - y0 + 1][px - x0 + 1] = (T)phid;
+        sphp[py - y0 + 1][px - x0 + 1] = hp;
+        return true;
+    };
+    auto fill = [&](int wx, int wy) {
+        OFF off[9];
+        T fw[9];
+        double ph;
+        pull_phi(x0 - 1 + wx, y0 - 1 + wy, off, fw, ph);
+    };
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int lx = threadIdx.x, ly = threadIdx.y + r * BY, x = x0 + lx, y = y0 + ly;
+        if (!inner && (x >= P.nx || y >= P.ny)) {
+            fill(lx + 1, ly + 1);
+            continue;
+        }
+        OFF off[9];
+        pull_phi(x, y, off, fo[r], phio[r]);
+        go[r][0] = S.template ld<T>(off[0], 9 * plB);
+#pragma unroll
+        for (int i = 1; i < Q; i++) go[r][i] = S.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
+        hu[r] = S.template ld<T>(off[0], 19 * plB);
+        hv[r] = S.template ld<T>(off[0], 20 * plB);
+    }
+    const int tid = threadIdx.y * TX + threadIdx.x;
+    for (int idx = tid; idx < 2 * WX + 2 * DTY; idx += TX * BY) {
+        if (idx < 2 * WX) fill(idx % WX, idx < WX ? 0 : DTY + 1);
+        else fill(idx < 2 * WX + DTY ? 0 : WX - 1, 1 + (idx - 2 * WX) % DTY);
+    }
+    __syncthreads();
+    wall_ghosts<T, DTY>(P, true, x0, y0, sphi, sphp);
 
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int r = 0; r < DTY / BY; r++) {
+#pragma unroll
+    for (int r = 0; r < R; r++) {
         const int lx = threadIdx.x, ly = threadIdx.y + r * BY;
         const int x = x0 + lx, y = y0 + ly;
         if (x >= P.nx || y >= P.ny) continue;
         const long long k = (long long)y * P.nx + x;
-        T f[9], g[9];
-        const double phid = node_phi(P, S, x, y, f);
-        for (int i = 0; i < Q; i++) g[i] = pull(S.g, P, i, x, y);
+        const T *f = fo[r], *g = go[r];
+        const double phid = phio[r];
         T gx, gy, lap, gxp = T(0), gyp = T(0), lp, php = sphp[ly + 1][lx + 1], up = T(0), vp = T(0);
         win_stencil<T, DTY>(sphi, lx + 1, ly + 1, gx, gy, lap);
         const T phi = sphi[ly + 1][lx + 1];
         if (!first) {
-            up = S.h[P.plane + k];
-            vp = S.h[2 * P.plane + k];
+            up = hu[r];
+            vp = hv[r];
         }
         if (P.grad == 1 && !first) {
             // local gradient scheme: grad phi by Eq. local, m^phiC of the previous level stored
             local_grad(P, f, g, phi, lap, php * up, php * vp, gx, gy);
             const Macro<T> M = macro<T, false, true>(P, g, phi, gx, gy, lap, first, php, T(0), T(0), up, vp, T(0),
-                                                     T(0), S.h[3 * P.plane + k], S.h[4 * P.plane + k]);
+                                                     T(0), S.template ld<T>((OFF)k * ES, 21 * plB), S.template ld<T>((OFF)k * ES, 22 * plB));
             diag_node(P, M, f, g, phid, first, php, k, scr, acc);
             continue;
         }
@@ -247,7 +297,9 @@ hipError_t launch_diagnostics(const KParams<T>& P, const char* state, const Layo
         k_diag1_ch<T, false><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, scr, partials);
     else if (P.model == 2)
         k_diag1_ch<T, true><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, scr, partials);
-    else k_diag1<T><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, scr, partials);
+    else if (L.buf_bytes < (size_t(1) << 32))
+        k_diag1<T, uint32_t><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, scr, partials);
+    else k_diag1<T, uint64_t><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, scr, partials);
     k_diag2<T><<<grd, blk, 0, s>>>(P, scr, partials);
     k_diag3<<<1, DIAG3_THREADS, 0, s>>>(partials, (int)(grd.x * grd.y), L.n, out);
     hipError_t e = hipGetLastError();

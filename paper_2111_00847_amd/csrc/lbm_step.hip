@@ -19,6 +19,7 @@
 // the per-node update for its nodes (lbm_fused.hpp).
 #include <cstdlib>
 
+#include "lbm_addr.hpp"
 #include "lbm_ch_step.hpp"
 #include "lbm_fused.hpp"
 #include "lbm_kernels.hpp"
@@ -140,9 +141,12 @@ static void launch_ch(const KParams<T>& P, char* state, const Layout& L, hipStre
 // ---------------------------------------------------------------- init / import / export
 // phi at (x, y) of a caller field, extended by the lattice's ghost rule:
 // periodic axes wrap; x-wall ghosts from the row, y-wall ghosts from the
-// (possibly x-ghost) column -- the same order as the LDS window.
+// (possibly x-ghost) column -- the same order as the LDS window.  The few nodes
+// beside a wall call it; inlined at each of their nine (or 81) positions it made
+// a kernel of 14000 instructions that runs once, from a cold instruction cache.
 template <typename T>
-__device__ T field_at(const KParams<T>& P, const T* phi, int x, int y) {
+__device__ __attribute__((noinline)) T field_at(ParamsPtr<T> params, const T* phi, int x, int y) {
+    const KParams<T> P = *(const KParams<T>*)params;
     if (!P.wall_x && (x < 0 || x >= P.nx)) x = x < 0 ? x + P.nx : x - P.nx;
     if (!P.wall_y && (y < 0 || y >= P.ny)) y = y < 0 ? y + P.ny : y - P.ny;
     auto col = [&](int xx, int yy) -> T {
@@ -159,6 +163,46 @@ __device__ T field_at(const KParams<T>& P, const T* phi, int x, int y) {
 // mu_phi of a caller field at (x, y) (Sec. 2), positions beyond a wall taking
 // the value of the first fluid node (x first, then y), periodic axes wrapping.
 template <typename T>
+__device__ __attribute__((noinline)) T mu_at(ParamsPtr<T> params, const T* phi, int x, int y) {
+    const KParams<T> P = *(const KParams<T>*)params;
+    if (x < 0 || x >= P.nx) x = P.wall_x ? (x < 0 ? 0 : P.nx - 1) : (x < 0 ? x + P.nx : x - P.nx);
+    if (y < 0 || y >= P.ny) y = P.wall_y ? (y < 0 ? 0 : P.ny - 1) : (y < 0 ? y + P.ny : y - P.ny);
+    T n_[3][3];
+#pragma unroll
+    for (int j = 0; j < 3; j++)
+#pragma unroll
+        for (int i = 0; i < 3; i++) n_[j][i] = field_at<T>(params, phi, x + i - 1, y + j - 1);
+    T gx, gy, lap;
+    stencil(n_[0][0], n_[0][1], n_[0][2], n_[1][0], n_[1][1], n_[1][2], n_[2][0], n_[2][1], n_[2][2], gx, gy, lap);
+    return chem_pot(P, n_[1][1], lap);
+}
+
+// The (2 H + 1)^2 neighbourhood of (x, y) of a caller field where none of it lies
+// beyond a wall (false otherwise): plain loads at wrapped offsets.
+template <int H, typename T>
+__device__ __forceinline__ bool open_neighbourhood(const KParams<T>& P, const T* phi, int x, int y,
+                                                   T (&v)[2 * H + 1][2 * H + 1]) {
+    if (P.nx < H || P.ny < H || (P.wall_x && (x < H || x >= P.nx - H)) || (P.wall_y && (y < H || y >= P.ny - H)))
+        return false;
+    long long col[2 * H + 1], row[2 * H + 1];
+#pragma unroll
+    for (int i = 0; i <= 2 * H; i++) {
+        int a = x + i - H, b = y + i - H;
+        a += a < 0 ? P.nx : 0;
+        b += b < 0 ? P.ny : 0;
+        col[i] = a - (a >= P.nx ? P.nx : 0);
+        row[i] = (long long)(b - (b >= P.ny ? P.ny : 0)) * P.nx;
+    }
+#pragma unroll
+    for (int j = 0; j <= 2 * H; j++)
+#pragma unroll
+        for (int i = 0; i <= 2 * H; i++) v[j][i] = phi[row[j] + col[i]];
+    return true;
+}
+
+// mu_phi of a caller field at (x, y) (Sec. 2), positions beyond a wall taking
+// the value of the first fluid node (x first, then y), periodic axes wrapping.
+template <typename T>
 __device__ T mu_at(const KParams<T>& P, const T* phi, int x, int y) {
     if (x < 0 || x >= P.nx) x = P.wall_x ? (x < 0 ? 0 : P.nx - 1) : (x < 0 ? x + P.nx : x - P.nx);
     if (y < 0 || y >= P.ny) y = P.wall_y ? (y < 0 ? 0 : P.ny - 1) : (y < 0 ? y + P.ny : y - P.ny);
@@ -170,26 +214,74 @@ __device__ T mu_at(const KParams<T>& P, const T* phi, int x, int y) {
     return chem_pot(P, n_[1][1], lap);
 }
 
-// Equilibria at every node into `eq` (f^eq planes 0..8, g^eq planes 9..17).
+// What a state needs besides its copy: the header and every level stamp.
+struct StateMeta {
+    StateHeader* header;
+    int64_t* stamp;
+    long long nstamp;
+    int64_t value;
+    int dtype;
+};
 template <typename T>
-__global__ void k_equilibrium(KParams<T> P, const T* phi0, const T* u0, const T* p0, T* eq) {
+__device__ __forceinline__ void set_meta(const KParams<T>& P, const StateMeta& m, long long i) {
+    if (i < m.nstamp) m.stamp[i] = m.value;
+    if (i == 0) {
+        m.header->magic = STATE_MAGIC;
+        m.header->nx = P.nx;
+        m.header->ny = P.ny;
+        m.header->dtype = m.dtype;
+    }
+}
+
+// Storing a state: the post-streaming population i of node (x, y) goes to the slot
+// that (x, y) pulls i from (neighbour_offsets; the map is one to one, so all
+// nodes' populations fill the copy).
+
+// The state of level 0: equilibria of the given fields in the pull
+// representation, zero history, header and stamps, in one pass (bound by HBM:
+// 1 to 4 planes read, 21 or 23 written).  CH: Cahn-Hilliard.
+template <typename T, bool CH, typename OFF>
+__global__ __launch_bounds__(256) void k_init(KParams<T> P, const T* phi0, const T* u0, const T* p0, char* dst_base,
+                                              StateMeta meta) {
+    const ParamsPtr<T> params = (ParamsPtr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr OFF ES = sizeof(T);
+    const OFF plB = (OFF)P.plane * ES;
+    const int nh = P.grad == 1 ? 5 : 3;
+    const CopyAddr<OFF> D(dst_base, (18 + nh) * plB);
     const long long n = (long long)P.nx * P.ny;
     for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
          k += (long long)gridDim.x * blockDim.x) {
+        set_meta(P, meta, k);   // no more stamps than nodes
         const int y = (int)(k / P.nx), x = (int)(k - (long long)y * P.nx);
         T n_[3][3];
-        for (int j = 0; j < 3; j++)
-            for (int i = 0; i < 3; i++) n_[j][i] = field_at(P, phi0, x + i - 1, y + j - 1);
+        if (!open_neighbourhood<1>(P, phi0, x, y, n_))
+#pragma unroll
+            for (int j = 0; j < 3; j++)
+#pragma unroll
+                for (int i = 0; i < 3; i++) n_[j][i] = field_at<T>(params, phi0, x + i - 1, y + j - 1);
         T gx, gy, lap;
         stencil(n_[0][0], n_[0][1], n_[0][2], n_[1][0], n_[1][1], n_[1][2], n_[2][0], n_[2][1], n_[2][2],
                 gx, gy, lap);
         const T phi = n_[1][1];
         const T u = u0 ? u0[k] : T(0), v = u0 ? u0[n + k] : T(0), p = p0 ? p0[k] : T(0);
         T lnx, lny, mx, my;
-        if (P.pf == 1) {   // Cahn-Hilliard: grad mu of the initial field, mu mirrored at walls
-            T mn[3][3];
-            for (int j = 0; j < 3; j++)
-                for (int i = 0; i < 3; i++) mn[j][i] = mu_at(P, phi0, x + i - 1, y + j - 1);
+        if (CH) {   // Cahn-Hilliard: grad mu of the initial field, mu mirrored at walls
+            T mn[3][3], w[5][5];
+            if (open_neighbourhood<2>(P, phi0, x, y, w)) {
+#pragma unroll
+                for (int j = 0; j < 3; j++)
+#pragma unroll
+                    for (int i = 0; i < 3; i++) {
+                        T a, b, c;
+                        win_stencil_at(w, i + 1, j + 1, a, b, c);
+                        mn[j][i] = chem_pot(P, w[j + 1][i + 1], c);
+                    }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 3; j++)
+#pragma unroll
+                    for (int i = 0; i < 3; i++) mn[j][i] = mu_at<T>(params, phi0, x + i - 1, y + j - 1);
+            }
             T gmx, gmy, lm;
             stencil(mn[0][0], mn[0][1], mn[0][2], mn[1][0], mn[1][1], mn[1][2], mn[2][0], mn[2][1], mn[2][2], gmx,
                     gmy, lm);
@@ -198,15 +290,21 @@ __global__ void k_equilibrium(KParams<T> P, const T* phi0, const T* u0, const T*
             mass_flux(P, phi, gx, gy, lnx, lny, mx, my);
         }
         const T rho = P.drho * (phi - P.phiB) + P.rhoB;
+        OFF off[9];
+        int xi, yi;
+        neighbour_offsets<T, OFF, -1>(P, false, x, y, off, xi, yi);
         T m[9], e[9];
         T mf[9] = {phi, T(-2) * phi, phi, phi * u, -phi * u, phi * v, -phi * v, T(0), T(0)};
-        if (P.pf == 1) {   // Eq. MfMRCH1
+        if (CH) {   // Eq. MfMRCH1
             const T mu = chem_pot(P, phi, lap);
             mf[1] = T(-4) * phi + T(2) * mu;
             mf[2] = T(4) * phi - T(3) * mu;
         }
         from_moments(mf, e);
-        for (int i = 0; i < Q; i++) eq[i * P.plane + k] = e[i];
+        D.template st<ST_PLAIN>(off[0], 0, rest_encode<T>((double)e[0], T(0), P.rest_w));
+#pragma unroll
+        for (int i = 1; i < Q; i++) D.template st<ST_PLAIN>(off[i], pair_plane(i) * plB, e[i]);
+        for (int j = 0; j < nh; j++) D.template st<ST_PLAIN>(off[0], (18 + j) * plB, T(0));
         T tr = T(3) * rho * (u * u + v * v) + T(3) * (u * mx + v * my);
         m[0] = P.rho0;
         m[1] = T(-4) * P.rho0 + T(6) * p + tr;
@@ -218,91 +316,196 @@ __global__ void k_equilibrium(KParams<T> P, const T* phi0, const T* u0, const T*
         m[7] = (u * mx - v * my) + rho * (u * u - v * v);
         m[8] = T(0.5) * ((u * my + v * mx) + T(2) * rho * u * v);
         from_moments(m, e);
-        for (int i = 0; i < Q; i++) eq[(9 + i) * P.plane + k] = e[i];
+        D.template st<ST_PLAIN>(off[0], 9 * plB, e[0]);
+#pragma unroll
+        for (int i = 1; i < Q; i++) D.template st<ST_PLAIN>(off[i], (9 + pair_plane(i)) * plB, e[i]);
     }
 }
 
-// Store post-streaming populations `post` (planes 0..17, level n) into the
-// pull representation of copy `dst`: slot (i, y) holds what (y + c_i) pulls,
-// or -- when y + c_i is beyond a wall -- what y itself pulls in direction
-// opp(i).  `post_stride` is the plane stride of `post`.
-template <typename T>
-__global__ void k_to_pull(KParams<T> P, const T* post, long long post_stride, char* dst_base) {
-    const Copy<T> D = copy_at<T>(dst_base, P.plane);
+// The state of level n from post-streaming populations f, g ([9][n] each) and
+// the history of level n - 1 (NULL: zeros), in one pass.
+template <typename T, typename OFF>
+__global__ __launch_bounds__(256) void k_import(KParams<T> P, const T* f, const T* g, const T* hist, char* dst_base,
+                                                StateMeta meta) {
+    constexpr OFF ES = sizeof(T);
+    const OFF plB = (OFF)P.plane * ES;
+    const int nh = P.grad == 1 ? 5 : 3;
+    const CopyAddr<OFF> D(dst_base, (18 + nh) * plB);
     const long long n = (long long)P.nx * P.ny;
     for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
          k += (long long)gridDim.x * blockDim.x) {
+        set_meta(P, meta, k);
         const int y = (int)(k / P.nx), x = (int)(k - (long long)y * P.nx);
-        for (int h = 0; h < 2; h++) {
-            const T* src = post + h * 9 * post_stride;
-            for (int i = 0; i < Q; i++) {
-                int tx = x + cx(i), ty = y + cy(i);
-                bool wall = false;
-                if (tx < 0 || tx >= P.nx) {
-                    if (P.wall_x) wall = true;
-                    else tx = tx < 0 ? tx + P.nx : tx - P.nx;
-                }
-                if (ty < 0 || ty >= P.ny) {
-                    if (P.wall_y) wall = true;
-                    else ty = ty < 0 ? ty + P.ny : ty - P.ny;
-                }
-                T val = wall ? src[opp(i) * post_stride + k] : src[i * post_stride + (long long)ty * P.nx + tx];
-                if (h == 1) D.g[i * P.plane + k] = val;
-                else if (i == 0) D.f0[k] = rest_encode<T>((double)val, D.h[k], P.rest_w);
-                else D.f[i * P.plane + k] = val;
-            }
-        }
+        T fv[9], gv[9], hv[5];
+#pragma unroll
+        for (int i = 0; i < Q; i++) fv[i] = f[i * n + k];
+#pragma unroll
+        for (int i = 0; i < Q; i++) gv[i] = g[i * n + k];
+#pragma unroll
+        for (int j = 0; j < 5; j++) hv[j] = hist && j < nh ? hist[j * n + k] : T(0);
+        OFF off[9];
+        int xi, yi;
+        neighbour_offsets<T, OFF, -1>(P, false, x, y, off, xi, yi);
+        D.template st<ST_PLAIN>(off[0], 0, rest_encode<T>((double)fv[0], hv[0], P.rest_w));
+#pragma unroll
+        for (int i = 1; i < Q; i++) D.template st<ST_PLAIN>(off[i], pair_plane(i) * plB, fv[i]);
+        D.template st<ST_PLAIN>(off[0], 9 * plB, gv[0]);
+#pragma unroll
+        for (int i = 1; i < Q; i++) D.template st<ST_PLAIN>(off[i], (9 + pair_plane(i)) * plB, gv[i]);
+#pragma unroll
+        for (int j = 0; j < 5; j++)
+            if (j < nh) D.template st<ST_PLAIN>(off[0], (18 + j) * plB, hv[j]);
     }
 }
 
-template <typename T>
-__global__ void k_export(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stamp, T* f, T* g,
-                         T* hist) {
+// Post-streaming populations and history of the current level: f, g [9][n],
+// hist [3][n] ([5][n] for the local gradient scheme), any NULL.
+template <typename T, typename OFF>
+__global__ __launch_bounds__(256) void k_export(KParams<T> P, const char* state, size_t off0, size_t off1,
+                                                size_t off_stamp, T* f, T* g, T* hist) {
+    constexpr OFF ES = sizeof(T);
+    const OFF plB = (OFF)P.plane * ES;
+    const int nh = P.grad == 1 ? 5 : 3;
     const int cur = stamp_copy(*reinterpret_cast<const int64_t*>(state + off_stamp));
-    const Copy<T> S = copy_at<T>(state + (cur ? off1 : off0), P.plane);
+    const CopyAddr<OFF> S(state + (cur ? off1 : off0), (18 + nh) * plB);
     const long long n = (long long)P.nx * P.ny;
     for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
          k += (long long)gridDim.x * blockDim.x) {
         const int y = (int)(k / P.nx), x = (int)(k - (long long)y * P.nx);
+        OFF off[9];
+        int xi, yi;
+        neighbour_offsets<T, OFF, -1>(P, false, x, y, off, xi, yi);
         if (f) {
-            f[k] = (T)rest_decode(S.f0[k], S.h[k], P.rest_w);
-            for (int i = 1; i < Q; i++) f[i * n + k] = pull(S.f, P, i, x, y);
+            T v[9];
+            v[0] = (T)rest_decode(S.template ld<T>(off[0], 0), S.template ld<T>(off[0], 18 * plB), P.rest_w);
+#pragma unroll
+            for (int i = 1; i < Q; i++) v[i] = S.template ld<T>(off[i], pair_plane(i) * plB);
+#pragma unroll
+            for (int i = 0; i < Q; i++) f[i * n + k] = v[i];
         }
-        if (g)
-            for (int i = 0; i < Q; i++) g[i * n + k] = pull(S.g, P, i, x, y);
+        if (g) {
+            T v[9];
+            v[0] = S.template ld<T>(off[0], 9 * plB);
+#pragma unroll
+            for (int i = 1; i < Q; i++) v[i] = S.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
+#pragma unroll
+            for (int i = 0; i < Q; i++) g[i * n + k] = v[i];
+        }
         if (hist)   // phi, u, v of level n-1 (and m^phiC of level n-1 for the local gradient scheme)
-            for (int j = 0; j < (P.grad == 1 ? 5 : 3); j++) hist[j * n + k] = S.h[j * P.plane + k];
+            for (int j = 0; j < nh; j++) hist[j * n + k] = S.template ld<T>(off[0], (18 + j) * plB);
     }
-}
-
-template <typename T>
-__global__ void k_copy_hist(KParams<T> P, const T* hist, char* dst_base) {
-    const Copy<T> D = copy_at<T>(dst_base, P.plane);
-    const long long n = (long long)P.nx * P.ny;
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
-         k += (long long)gridDim.x * blockDim.x)
-        for (int j = 0; j < (P.grad == 1 ? 5 : 3); j++) D.h[j * P.plane + k] = hist ? hist[j * n + k] : T(0);
-}
-
-__global__ void k_set_header(StateHeader* H, int nx, int ny, int dtype) {
-    H->magic = STATE_MAGIC;
-    H->nx = nx;
-    H->ny = ny;
-    H->dtype = dtype;
-}
-
-__global__ void k_set_stamps(int64_t* stamp, long long n, int64_t value) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-        stamp[i] = value;
 }
 
 // Hydrostatic pressure of the two fluids at rest (the initial pressure of the
 // gravity-driven set-ups): rho from the density law of Sec. 2 at phi0,
-// dp/dy = (rho - rho_ref) g_y integrated down every column by the trapezoid
-// rule from p = 0 at the top row, then the mean taken out.  One workgroup:
-// every thread walks its columns twice (FP64 sums; the second walk subtracts
-// the mean that the block reduction of the first one gives).
-constexpr int HYDRO_THREADS = 1024;
+// dp/dy = f, f = (rho - rho_ref) g_y, integrated down every column by the
+// trapezoid rule from p = 0 at the top row, then the mean taken out, in FP64.
+// A column is a serial chain of ny additions (kept in that order: an instability
+// that starts from this field amplifies its rounding).  The chain itself is
+// short; what took 482 us at 256 x 1024 FP32 (11.3 ms at
+// 4096 x 4096) was one workgroup loading a row between every two additions.  So
+// a workgroup takes 16 columns and stages 256 rows of f at a time in LDS, the
+// next rows' loads running while 16 of its threads run the chains (24 and 33 us for
+// the two passes at 256 x 1024; chains fed by waves of their own, and reading LDS a
+// group of rows ahead, were no faster: 27 to 40 us, and 21 and 33):
+//   k_hydro_cols, SUMS  the sum of p down every column, kept in the column's own
+//                       first bytes of p0 (rows 0 and 1 in FP32, row 0 in FP64);
+//   k_hydro_mean        the mean, left in the first bytes of every workgroup's
+//                       first column;
+//   k_hydro_cols        p less the mean.
+constexpr int HYDRO_THREADS = 1024, HYDRO_COLS = 16, HYDRO_ROWS = 256, HYDRO_STAGE = 256;
+
+// The double kept in column x's first bytes of p0.
+template <typename T>
+__device__ __forceinline__ void put_col(T* p0, int nx, int x, double v) {
+    if constexpr (sizeof(T) == 8) p0[x] = v;
+    else {
+        const uint64_t w = __builtin_bit_cast(uint64_t, v);
+        p0[x] = __builtin_bit_cast(T, (uint32_t)w);
+        p0[nx + x] = __builtin_bit_cast(T, (uint32_t)(w >> 32));
+    }
+}
+template <typename T>
+__device__ __forceinline__ double get_col(const T* p0, int nx, int x) {
+    if constexpr (sizeof(T) == 8) return p0[x];
+    else return __builtin_bit_cast(double, (uint64_t)__builtin_bit_cast(uint32_t, p0[x]) |
+                                               (uint64_t)__builtin_bit_cast(uint32_t, p0[nx + x]) << 32);
+}
+
+template <typename T, bool SUMS>
+__global__ __launch_bounds__(HYDRO_STAGE) void k_hydro_cols(KParams<T> P, const T* __restrict__ phi0,
+                                                            T* __restrict__ p0) {
+    constexpr int PER = HYDRO_ROWS * HYDRO_COLS / HYDRO_STAGE;   // staged elements per thread
+    __shared__ double f[2][HYDRO_ROWS][HYDRO_COLS + 1];
+    const int nx = P.nx, ny = P.ny, x0 = blockIdx.x * HYDRO_COLS, tid = threadIdx.x;
+    const double gy = (double)P.gy, drho = (double)P.drho, rhoB = (double)P.rhoB, rref = (double)P.rho_ref,
+                 phiB = (double)P.phiB;
+    const double mean = SUMS ? 0.0 : get_col(p0, nx, x0);   // read before the first barrier, overwritten after it
+    const int chunks = (ny + HYDRO_ROWS - 1) / HYDRO_ROWS;
+    T v[PER];
+    // chunk c: rows ny - 1 - c HYDRO_ROWS downwards, element e of it row e / COLS, column e % COLS
+    auto load = [&](int c) {
+#pragma unroll
+        for (int q = 0; q < PER; q++) {
+            const int e = tid + q * HYDRO_STAGE, j = ny - 1 - c * HYDRO_ROWS - e / HYDRO_COLS, x = x0 + e % HYDRO_COLS;
+            v[q] = j >= 0 && x < nx ? phi0[(long long)j * nx + x] : T(0);
+        }
+    };
+    auto stage = [&](int c) {
+#pragma unroll
+        for (int q = 0; q < PER; q++) {
+            const int e = tid + q * HYDRO_STAGE;
+            f[c & 1][e / HYDRO_COLS][e % HYDRO_COLS] = (drho * ((double)v[q] - phiB) + rhoB - rref) * gy;
+        }
+    };
+    load(0);
+    stage(0);
+    __syncthreads();
+    double p = 0.0, fu = 0.0, acc = 0.0;
+    for (int c = 0; c < chunks; c++) {
+        if (c + 1 < chunks) load(c + 1);
+        const int rows = ny - c * HYDRO_ROWS < HYDRO_ROWS ? ny - c * HYDRO_ROWS : HYDRO_ROWS;
+        if (tid < HYDRO_COLS) {
+            double (*col)[HYDRO_COLS + 1] = f[c & 1];
+#pragma unroll 8
+            for (int r = 0; r < rows; r++) {
+                const double fj = col[r][tid];
+                if (c > 0 || r > 0) p -= 0.5 * (fj + fu);
+                fu = fj;
+                acc += p;
+                if (!SUMS) col[r][tid] = p - mean;
+            }
+        }
+        __syncthreads();
+        if (!SUMS)
+#pragma unroll
+            for (int q = 0; q < PER; q++) {
+                const int e = tid + q * HYDRO_STAGE, r = e / HYDRO_COLS, x = x0 + e % HYDRO_COLS;
+                if (r < rows && x < nx) p0[(long long)(ny - 1 - c * HYDRO_ROWS - r) * nx + x] = (T)f[c & 1][r][e % HYDRO_COLS];
+            }
+        if (c + 1 < chunks) stage(c + 1);
+        __syncthreads();
+    }
+    if (SUMS && tid < HYDRO_COLS && x0 + tid < nx) put_col(p0, nx, x0 + tid, acc);
+}
+
+template <typename T>
+__global__ __launch_bounds__(HYDRO_THREADS) void k_hydro_mean(KParams<T> P, T* p0) {
+    __shared__ double red[HYDRO_THREADS / 64];
+    double acc = 0.0;
+    for (int x = threadIdx.x; x < P.nx; x += HYDRO_THREADS) acc += get_col(p0, P.nx, x);
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();   // every column's sum is read
+    double t = 0.0;
+    for (int w = 0; w < HYDRO_THREADS / 64; w++) t += red[w];
+    const double mean = t / ((double)P.nx * (double)P.ny);
+    for (int x = threadIdx.x * HYDRO_COLS; x < P.nx; x += HYDRO_THREADS * HYDRO_COLS) put_col(p0, P.nx, x, mean);
+}
+
+// The same by one workgroup, every thread walking its columns twice (the second
+// walk subtracts the mean the first one gives): for a p0 that overlaps phi0, whose
+// bytes hold no sums before they are read, and for one row.
 
 template <typename T>
 __global__ __launch_bounds__(HYDRO_THREADS) void k_hydrostatic(KParams<T> P, const T* phi0, T* p0) {
@@ -454,57 +657,54 @@ hipError_t launch_moments(const KParams<T>& P, const char* state, const Layout& 
     return hipGetLastError();
 }
 
+static StateMeta state_meta(char* state, const Layout& L, int dtype, int64_t stamp) {
+    return StateMeta{reinterpret_cast<StateHeader*>(state), reinterpret_cast<int64_t*>(state + L.off_stamp),
+                     (long long)L.nstamp, stamp, dtype};
+}
+
 template <typename T>
 hipError_t launch_init(const KParams<T>& P, char* state, const Layout& L, const T* phi0, const T* u0,
                        const T* p0, int dtype, hipStream_t s) {
-    T* scratch = reinterpret_cast<T*>(state + L.off_buf[1]);   // 18 planes of T fit in one copy
-    char* dst = state + L.off_buf[0];
-    int g = grid1d(L.n);
-    k_equilibrium<T><<<g, 256, 0, s>>>(P, phi0, u0, p0, scratch);
-    k_copy_hist<T><<<g, 256, 0, s>>>(P, nullptr, dst);   // before k_to_pull: f_0 is stored relative to it
-    k_to_pull<T><<<g, 256, 0, s>>>(P, scratch, P.plane, dst);
-    k_set_header<<<1, 1, 0, s>>>(reinterpret_cast<StateHeader*>(state), P.nx, P.ny, dtype);
-    k_set_stamps<<<grid1d((long long)L.nstamp), 256, 0, s>>>(reinterpret_cast<int64_t*>(state + L.off_stamp),
-                                                              (long long)L.nstamp, stamp_of(0, 0));
+    const StateMeta meta = state_meta(state, L, dtype, stamp_of(0, 0));
+    auto go = [&](auto kernel) { kernel<<<grid1d(L.n), 256, 0, s>>>(P, phi0, u0, p0, state + L.off_buf[0], meta); };
+    if (P.pf == 1) small_copy(L) ? go(k_init<T, true, uint32_t>) : go(k_init<T, true, uint64_t>);
+    else small_copy(L) ? go(k_init<T, false, uint32_t>) : go(k_init<T, false, uint64_t>);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_hydrostatic(const KParams<T>& P, const T* phi0, T* p0, hipStream_t s) {
-    k_hydrostatic<T><<<1, HYDRO_THREADS, 0, s>>>(P, phi0, p0);
+    const long long n = (long long)P.nx * P.ny;
+    if (P.ny < 2 || (p0 < phi0 + n && phi0 < p0 + n)) {
+        k_hydrostatic<T><<<1, HYDRO_THREADS, 0, s>>>(P, phi0, p0);
+        return hipGetLastError();
+    }
+    const int g = (P.nx + HYDRO_COLS - 1) / HYDRO_COLS;
+    k_hydro_cols<T, true><<<g, HYDRO_STAGE, 0, s>>>(P, phi0, p0);
+    k_hydro_mean<T><<<1, HYDRO_THREADS, 0, s>>>(P, p0);
+    k_hydro_cols<T, false><<<g, HYDRO_STAGE, 0, s>>>(P, phi0, p0);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_import(const KParams<T>& P, char* state, const Layout& L, const T* f, const T* g,
                          const T* hist, int64_t step, int dtype, hipStream_t s) {
-    // f and g are separate caller arrays of [9][n]; stage them contiguously in
-    // the other copy, which the next step overwrites anyway.
-    int cur = (int)(step & 1);
-    char* dst = state + L.off_buf[cur];
-    T* stage = reinterpret_cast<T*>(state + L.off_buf[1 - cur]);
-    size_t bytes9 = (size_t)9 * L.n * sizeof(T);
-    hipError_t e = hipMemcpy2DAsync(stage, (size_t)P.plane * sizeof(T), f, (size_t)L.n * sizeof(T),
-                                    (size_t)L.n * sizeof(T), 9, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    e = hipMemcpy2DAsync(stage + 9 * P.plane, (size_t)P.plane * sizeof(T), g, (size_t)L.n * sizeof(T),
-                         (size_t)L.n * sizeof(T), 9, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    (void)bytes9;
-    int gr = grid1d(L.n);
-    k_copy_hist<T><<<gr, 256, 0, s>>>(P, step > 0 ? hist : nullptr, dst);   // before k_to_pull (f_0)
-    k_to_pull<T><<<gr, 256, 0, s>>>(P, stage, P.plane, dst);
-    k_set_header<<<1, 1, 0, s>>>(reinterpret_cast<StateHeader*>(state), P.nx, P.ny, dtype);
-    k_set_stamps<<<grid1d((long long)L.nstamp), 256, 0, s>>>(reinterpret_cast<int64_t*>(state + L.off_stamp),
-                                                              (long long)L.nstamp, stamp_of(step, cur));
+    const int cur = (int)(step & 1);
+    const StateMeta meta = state_meta(state, L, dtype, stamp_of(step, cur));
+    auto go = [&](auto kernel) {
+        kernel<<<grid1d(L.n), 256, 0, s>>>(P, f, g, step > 0 ? hist : nullptr, state + L.off_buf[cur], meta);
+    };
+    small_copy(L) ? go(k_import<T, uint32_t>) : go(k_import<T, uint64_t>);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_export(const KParams<T>& P, const char* state, const Layout& L, T* f, T* g, T* hist,
                          hipStream_t s) {
-    k_export<T><<<grid1d(L.n), 256, 0, s>>>(P, const_cast<char*>(state), L.off_buf[0], L.off_buf[1], L.off_stamp, f,
-                                             g, hist);
+    auto go = [&](auto kernel) {
+        kernel<<<grid1d(L.n), 256, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, f, g, hist);
+    };
+    small_copy(L) ? go(k_export<T, uint32_t>) : go(k_export<T, uint64_t>);
     return hipGetLastError();
 }
 

@@ -69,20 +69,6 @@ struct Step2Lds {
     T mxa[LOCAL ? NA : 1], mya[LOCAL ? NA : 1];
 };
 
-// The kernel parameters in constant memory.  params_at() reads the fields that
-// the code after it uses.  In FP64 each phase reads them anew, which keeps them
-// out of scalar registers in between: held from end to end they spilled into
-// vector lanes, 240 of the 2900 vector instructions of the body (1999 x 2203:
-// 237 to 228 us per level).  The FP32 body has registers for them.
-template <typename T>
-using ParamsPtr = const __attribute__((address_space(4))) KParams<T>*;
-
-template <typename T>
-__device__ __forceinline__ KParams<T> params_at(ParamsPtr<T> p) {
-    if constexpr (sizeof(T) == 8) asm volatile("" : "+s"(p));
-    return *(const KParams<T>*)p;
-}
-
 // Two levels of one TW x TY tile, with the LDS `L` of the workgroup of NT
 // threads (64 x NT/64).  `tile` (StateTile, TapeTile) says which tile, where its
 // level is read and where level + 2 goes.  MID also stores the tile's

@@ -64,37 +64,6 @@ __device__ __forceinline__ void wall_ghosts(const KParams<T>& P, bool need_prev,
     }
 }
 
-// Fill the LDS window of phi (and of phi_prev when `need_prev`) for the tile
-// at (x0, y0).  Window (wx, wy) is node (x0 - 1 + wx, y0 - 1 + wy).  Periodic
-// axes wrap; wall ghosts follow Eq. (Dwetting): x-walls first, then y-walls
-// across the extended rows, which fixes the corners.
-template <typename T, int TY>
-__device__ __forceinline__ void fill_window(const KParams<T>& P, const Copy<T>& C, bool need_prev, int x0,
-                                            int y0, T (*sphi)[TX + 3], T (*sphp)[TX + 3]) {
-    constexpr int WX = TX + 2, WY = TY + 2;
-    const int tid = threadIdx.y * TX + threadIdx.x;
-    for (int idx = tid; idx < WX * WY; idx += TX * BY) {
-        int wy = idx / WX, wx = idx - wy * WX;
-        int gx = x0 - 1 + wx, gy = y0 - 1 + wy;
-        if (gx > P.nx || gy > P.ny) continue;
-        bool ghost = false;
-        if (gx < 0 || gx >= P.nx) {
-            if (P.wall_x) ghost = true;
-            else gx = gx < 0 ? gx + P.nx : gx - P.nx;
-        }
-        if (gy < 0 || gy >= P.ny) {
-            if (P.wall_y) ghost = true;
-            else gy = gy < 0 ? gy + P.ny : gy - P.ny;
-        }
-        if (ghost) continue;
-        T fw[9];
-        sphi[wy][wx] = (T)node_phi(P, C, gx, gy, fw);
-        if (need_prev) sphp[wy][wx] = C.h[(long long)gy * P.nx + gx];
-    }
-    __syncthreads();
-    wall_ghosts<T, TY>(P, need_prev, x0, y0, sphi, sphp);
-}
-
 // The same stencils on any 2-D window array, centred at (wx, wy).
 template <typename A, typename T>
 __device__ __forceinline__ void win_stencil_at(const A& s, int wx, int wy, T& gx, T& gy, T& lap) {
