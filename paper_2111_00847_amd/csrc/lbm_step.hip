@@ -408,8 +408,10 @@ __global__ __launch_bounds__(256) void k_export(KParams<T> P, const char* state,
 // next rows' loads running while 16 of its threads run the chains (24 and 33 us for
 // the two passes at 256 x 1024; chains fed by waves of their own, and reading LDS a
 // group of rows ahead, were no faster: 27 to 40 us, and 21 and 33):
-//   k_hydro_cols, SUMS  the sum of p down every column, kept in the column's own
-//                       first bytes of p0 (rows 0 and 1 in FP32, row 0 in FP64);
+//   k_hydro_cols, SUMS  the sum of p down columns x, x + 1024, ... (the order of the
+//                       additions of one workgroup of 1024 threads), kept in column
+//                       x's own first bytes of p0 (rows 0 and 1 in FP32, row 0 in
+//                       FP64);
 //   k_hydro_mean        the mean, left in the first bytes of every workgroup's
 //                       first column;
 //   k_hydro_cols        p less the mean.
@@ -437,9 +439,10 @@ __global__ __launch_bounds__(HYDRO_STAGE) void k_hydro_cols(KParams<T> P, const 
                                                             T* __restrict__ p0) {
     constexpr int PER = HYDRO_ROWS * HYDRO_COLS / HYDRO_STAGE;   // staged elements per thread
     __shared__ double f[2][HYDRO_ROWS][HYDRO_COLS + 1];
-    const int nx = P.nx, ny = P.ny, x0 = blockIdx.x * HYDRO_COLS, tid = threadIdx.x;
+    const int nx = P.nx, ny = P.ny, tid = threadIdx.x;
     const double gy = (double)P.gy, drho = (double)P.drho, rhoB = (double)P.rhoB, rref = (double)P.rho_ref,
                  phiB = (double)P.phiB;
+    int x0 = blockIdx.x * HYDRO_COLS;
     const double mean = SUMS ? 0.0 : get_col(p0, nx, x0);   // read before the first barrier, overwritten after it
     const int chunks = (ny + HYDRO_ROWS - 1) / HYDRO_ROWS;
     T v[PER];
@@ -458,34 +461,38 @@ __global__ __launch_bounds__(HYDRO_STAGE) void k_hydro_cols(KParams<T> P, const 
             f[c & 1][e / HYDRO_COLS][e % HYDRO_COLS] = (drho * ((double)v[q] - phiB) + rhoB - rref) * gy;
         }
     };
-    load(0);
-    stage(0);
-    __syncthreads();
-    double p = 0.0, fu = 0.0, acc = 0.0;
-    for (int c = 0; c < chunks; c++) {
-        if (c + 1 < chunks) load(c + 1);
-        const int rows = ny - c * HYDRO_ROWS < HYDRO_ROWS ? ny - c * HYDRO_ROWS : HYDRO_ROWS;
-        if (tid < HYDRO_COLS) {
-            double (*col)[HYDRO_COLS + 1] = f[c & 1];
+    double acc = 0.0;
+    for (; x0 < nx; x0 += SUMS ? HYDRO_THREADS : nx) {
+        load(0);
+        stage(0);
+        __syncthreads();
+        double p = 0.0, fu = 0.0;
+        for (int c = 0; c < chunks; c++) {
+            if (c + 1 < chunks) load(c + 1);
+            const int rows = ny - c * HYDRO_ROWS < HYDRO_ROWS ? ny - c * HYDRO_ROWS : HYDRO_ROWS;
+            if (tid < HYDRO_COLS && x0 + tid < nx) {
+                double (*col)[HYDRO_COLS + 1] = f[c & 1];
 #pragma unroll 8
-            for (int r = 0; r < rows; r++) {
-                const double fj = col[r][tid];
-                if (c > 0 || r > 0) p -= 0.5 * (fj + fu);
-                fu = fj;
-                acc += p;
-                if (!SUMS) col[r][tid] = p - mean;
+                for (int r = 0; r < rows; r++) {
+                    const double fj = col[r][tid];
+                    if (c > 0 || r > 0) p -= 0.5 * (fj + fu);
+                    fu = fj;
+                    acc += p;
+                    if (!SUMS) col[r][tid] = p - mean;
+                }
             }
-        }
-        __syncthreads();
-        if (!SUMS)
+            __syncthreads();
+            if (!SUMS)
 #pragma unroll
-            for (int q = 0; q < PER; q++) {
-                const int e = tid + q * HYDRO_STAGE, r = e / HYDRO_COLS, x = x0 + e % HYDRO_COLS;
-                if (r < rows && x < nx) p0[(long long)(ny - 1 - c * HYDRO_ROWS - r) * nx + x] = (T)f[c & 1][r][e % HYDRO_COLS];
-            }
-        if (c + 1 < chunks) stage(c + 1);
-        __syncthreads();
+                for (int q = 0; q < PER; q++) {
+                    const int e = tid + q * HYDRO_STAGE, r = e / HYDRO_COLS, x = x0 + e % HYDRO_COLS;
+                    if (r < rows && x < nx) p0[(long long)(ny - 1 - c * HYDRO_ROWS - r) * nx + x] = (T)f[c & 1][r][e % HYDRO_COLS];
+                }
+            if (c + 1 < chunks) stage(c + 1);
+            __syncthreads();
+        }
     }
+    x0 = blockIdx.x * HYDRO_COLS;
     if (SUMS && tid < HYDRO_COLS && x0 + tid < nx) put_col(p0, nx, x0 + tid, acc);
 }
 
@@ -493,7 +500,7 @@ template <typename T>
 __global__ __launch_bounds__(HYDRO_THREADS) void k_hydro_mean(KParams<T> P, T* p0) {
     __shared__ double red[HYDRO_THREADS / 64];
     double acc = 0.0;
-    for (int x = threadIdx.x; x < P.nx; x += HYDRO_THREADS) acc += get_col(p0, P.nx, x);
+    if ((int)threadIdx.x < P.nx) acc = get_col(p0, P.nx, threadIdx.x);
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();   // every column's sum is read
@@ -680,7 +687,7 @@ hipError_t launch_hydrostatic(const KParams<T>& P, const T* phi0, T* p0, hipStre
         return hipGetLastError();
     }
     const int g = (P.nx + HYDRO_COLS - 1) / HYDRO_COLS;
-    k_hydro_cols<T, true><<<g, HYDRO_STAGE, 0, s>>>(P, phi0, p0);
+    k_hydro_cols<T, true><<<g < HYDRO_THREADS / HYDRO_COLS ? g : HYDRO_THREADS / HYDRO_COLS, HYDRO_STAGE, 0, s>>>(P, phi0, p0);
     k_hydro_mean<T><<<1, HYDRO_THREADS, 0, s>>>(P, p0);
     k_hydro_cols<T, false><<<g, HYDRO_STAGE, 0, s>>>(P, phi0, p0);
     return hipGetLastError();
