@@ -275,10 +275,9 @@ int lbm_adjoint_import(const lbm_params *p, void *adj, const void *fbar, const v
  * node per thread; those cases equal the lone runs to rounding (the tile height may
  * differ), the plain Allen-Cahn cases bitwise.  A batch whose every case runs
  * the plain Allen-Cahn step (stencil gradients, present or original model)
- * advances two levels per launch as lbm_step does (64 x 8 tiles; an odd step
- * count ends on a one-level launch) when it has at least 256 such tiles, or
- * whatever its size with LBM_TWO_LEVEL=1 in the environment when the plan is
- * made (never with LBM_TWO_LEVEL=0).  The plan is
+ * advances two levels per launch as lbm_step does (an odd step count ends on a
+ * one-level launch; never with LBM_TWO_LEVEL=0 in the environment when the plan
+ * is made).  The plan is
  * library-owned (a small device table of the cases and, once lbm_batch_step
  * runs on a non-NULL stream with nsteps >= 32 that the caller is not
  * capturing, a captured hipGraph of 32 steps for that state and stream). */
@@ -311,7 +310,9 @@ int lbm_batch_step(lbm_batch *batch, void *state, int64_t nsteps, void *stream);
  * per launch, work items per step (any pointer may be NULL). */
 int lbm_batch_tuning(const lbm_batch *batch, int32_t *tile_rows, int32_t *thread_rows, int32_t *grid,
                      int32_t *items);
-/* Levels one launch of the plan advances (1 or 2; host *levels). */
+/* Levels per crossing of the batch state (1 or 2; host *levels), by the rule of
+ * lbm_levels_per_launch over all cases' tiles; as there, smaller batches report 1
+ * and fold levels as the plan finds best. */
 int lbm_batch_levels_per_launch(const lbm_batch *batch, int32_t *levels);
 int lbm_batch_destroy(lbm_batch *batch);
 
@@ -322,7 +323,7 @@ int lbm_batch_destroy(lbm_batch *batch);
  * lbm_batch_case_offset give for the same cases, initialised by
  * lbm_batch_init or by lbm_init of every case at its offset) exactly as
  * lbm_batch_step does with an untuned plan of the same cases (8-row tiles,
- * one workgroup per work item, two levels per launch under the same rule,
+ * one workgroup per work item, two levels per launch where the plan takes them,
  * LBM_TWO_LEVEL read at every call), without a plan and without allocating: the
  * case table (at most LBM_NOALLOC_MAX_CASES cases, about 140 KB) lives in a
  * fixed device array of the library that every GPU it runs on holds until

@@ -2,6 +2,8 @@
 // adjoint): planes through a uniform base, nodes through one byte offset.
 #pragma once
 
+#include <type_traits>
+
 #include "lbm_device.hpp"
 
 namespace lbm {
@@ -56,18 +58,33 @@ struct CopyAddr<uint64_t> {
     }
 };
 
-// The kernel parameters in constant memory.  params_at() reads the fields that
-// the code after it uses.  In FP64 each phase reads them anew, which keeps them
-// out of scalar registers in between: held from end to end they spilled into
-// vector lanes, 240 of the 2900 vector instructions of the body (1999 x 2203:
-// 237 to 228 us per level).  The FP32 body has registers for them.
+// The kernel parameters of a tile body: by value, or (RELOAD) in constant memory,
+// from which params_at() reads the fields that the code after it uses anew, which
+// keeps them out of scalar registers in between.
 template <typename T>
 using ParamsPtr = const __attribute__((address_space(4))) KParams<T>*;
+template <typename T, bool RELOAD>
+using BodyParams = typename std::conditional<RELOAD, ParamsPtr<T>, KParams<T>>::type;
 
 template <typename T>
 __device__ __forceinline__ KParams<T> params_at(ParamsPtr<T> p) {
-    if constexpr (sizeof(T) == 8) asm volatile("" : "+s"(p));
+    asm volatile("" : "+s"(p));
     return *(const KParams<T>*)p;
+}
+template <typename T>
+__device__ __forceinline__ const KParams<T>& params_at(const KParams<T>& p) {
+    return p;
+}
+// From a kernel's first argument P, or from memory that the launch only reads.
+template <bool RELOAD, typename T>
+__device__ __forceinline__ BodyParams<T, RELOAD> kernel_params(const KParams<T>& P) {
+    if constexpr (RELOAD) return (ParamsPtr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+    else return P;
+}
+template <bool RELOAD, typename T>
+__device__ __forceinline__ BodyParams<T, RELOAD> memory_params(const KParams<T>& P) {
+    if constexpr (RELOAD) return (ParamsPtr<T>)&P;
+    else return P;
 }
 
 // Node of region position p on an axis of n nodes; -1 beyond a wall.  Periodic

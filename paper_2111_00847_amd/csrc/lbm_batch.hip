@@ -99,25 +99,28 @@ void k_step_batch(const BatchCase<T>* __restrict__ cases, int ncases, int nitems
     }
 }
 
-// Two levels per launch: work item blockIdx.x, one 64 x 8 tile of one case, per
-// workgroup of 64 x 8 threads (items of a case table for 8-row tiles).  One
-// item per workgroup: a loop over items (a persistent grid) doubles the
-// registers of the body (169 against 86 VGPRs in FP32).  PER_ITEM: the table
+// Two levels per launch: one work item, a TW x TY tile of one case, per workgroup
+// of NT threads, items dealt to the XCDs in bands so that neighbouring tiles share
+// an L2 (us per level, 32 x 8 tiles, against items in launch order: 8 cases FP32
+// 13.6 / 17.1, 20 cases 30.1 / 38.4, 64 cases 100.6 / 107.8).  One item per workgroup: a loop over items (a
+// persistent grid) doubles the registers of the body.  PER_ITEM: the table
 // holds one entry per item (its case's), so that the workgroup reads its case
 // directly instead of counting item_begin over the cases first (one round
 // trip and a barrier fewer before the tile's loads).
-template <typename T, bool NTS, bool PER_ITEM = false>
-__global__ __launch_bounds__(TX * 8) void k_step2_batch(const BatchCase<T>* __restrict__ cases, int ncases,
-                                                       int nitems, char* batch_state) {
-    __shared__ Step2Lds<T, TX, 8> L;
-    const int w = blockIdx.x;
-    if (w >= nitems) return;   // uniform over the workgroup
-    const BatchCase<T>& C = cases[PER_ITEM ? w : batch_case(cases, ncases, w, TX * 8)];
+template <typename T, int TW, int TY, int NT, bool NTS, bool PER_ITEM>
+__global__ __launch_bounds__(NT) void k_step2_batch(const BatchCase<T>* __restrict__ cases, int ncases, int nitems,
+                                                    char* batch_state) {
+    __shared__ Step2Lds<T, TW, TY> L;
+    const int w = xcd_band(blockIdx.x, nitems);
+    const BatchCase<T>& C = cases[PER_ITEM ? w : batch_case(cases, ncases, w, NT)];
     const int local = w - C.item_begin;
     const StateTile tile{batch_state + C.base, C.off0, C.off1, C.off_stamp, C.share, local, local % C.ntx,
                          local / C.ntx, 0};
-    if (C.P.rates_std) step2_body<T, TX, 8, TX * 8, true, NTS>((ParamsPtr<T>)&C.P, tile, L);
-    else step2_body<T, TX, 8, TX * 8, false, NTS>((ParamsPtr<T>)&C.P, tile, L);
+    auto body = [&](auto params) {
+        if (C.P.rates_std) step2_body<T, TW, TY, NT, true, NTS>(params, tile, L);
+        else step2_body<T, TW, TY, NT, false, NTS>(params, tile, L);
+    };
+    body(memory_params<step2_reload<T>(TW, TY, NT)>(C.P));
 }
 
 // Batches with two-node-window or local-gradient cases: 64 x TY threads (one
@@ -195,8 +198,10 @@ struct lbm_batch {
     void* d_cases = nullptr;
     int cus = 256;
     // two levels per launch (every case runs the plain Allen-Cahn step), on a
-    // case table of 8-row tiles
+    // table of items of the tile shape `shape2`; two_level: what
+    // lbm_batch_levels_per_launch reports (the size rule)
     bool two_level = false;
+    lbm::Step2Shape shape2 = lbm::S2_NONE;
     void* d_cases2 = nullptr;
     int nitems2 = 0;
     // graph of `graph_steps` levels for (graph_state, graph_stream)
@@ -208,17 +213,17 @@ struct lbm_batch {
 
 namespace {
 
-int tiles_for(const lbm_params& p, int ty, int* ntx, int* nty) {
-    *ntx = (p.nx + TX - 1) / TX;
+int tiles_for(const lbm_params& p, int tw, int ty, int* ntx, int* nty) {
+    *ntx = (p.nx + tw - 1) / tw;
     *nty = (p.ny + ty - 1) / ty;
     return *ntx * *nty;
 }
 
-// Case table of a batch for tiles of `ty` rows: parameters, state offsets and
+// Case table of a batch for tiles of tw x ty nodes: parameters, state offsets and
 // the first work item of every case; returns the number of work items.
 template <typename T>
-int fill_cases(const lbm_params* params, const Layout* layouts, const size_t* base, int ncases, int ty,
-               BatchCase<T>* h) {
+int fill_cases(const lbm_params* params, const Layout* layouts, const size_t* base, int ncases, int tw,
+               int ty, BatchCase<T>* h) {
     int items = 0;
     for (int c = 0; c < ncases; c++) {
         BatchCase<T>& C = h[c];
@@ -234,7 +239,7 @@ int fill_cases(const lbm_params* params, const Layout* layouts, const size_t* ba
                  : q.model == LBM_MODEL_CORRECTED ? 2
                  : q.grad_scheme == LBM_GRAD_LOCAL ? 3
                                                    : 0;
-        const int tiles = tiles_for(params[c], ty, &C.ntx, &C.nty);
+        const int tiles = tiles_for(params[c], tw, ty, &C.ntx, &C.nty);
         C.share = stamp_share((long long)layouts[c].nstamp, tiles);
         items += tiles;
     }
@@ -244,7 +249,7 @@ int fill_cases(const lbm_params* params, const Layout* layouts, const size_t* ba
 template <typename T>
 hipError_t upload_cases(lbm_batch* B, int ty) {
     std::vector<BatchCase<T>> h(B->ncases);
-    B->nitems = fill_cases<T>(B->params.data(), B->layouts.data(), B->base.data(), B->ncases, ty, h.data());
+    B->nitems = fill_cases<T>(B->params.data(), B->layouts.data(), B->base.data(), B->ncases, TX, ty, h.data());
     if (!B->d_cases) {
         hipError_t e = hipMalloc(&B->d_cases, sizeof(BatchCase<T>) * B->ncases);
         if (e != hipSuccess) return e;
@@ -252,11 +257,19 @@ hipError_t upload_cases(lbm_batch* B, int ty) {
     return hipMemcpy(B->d_cases, h.data(), sizeof(BatchCase<T>) * B->ncases, hipMemcpyHostToDevice);
 }
 
-// The case table of the two-level launch (8-row tiles).
+// Nodes of a tile of the two-level launch.
+void step2_tile_size(Step2Shape shape, int* tw, int* ty) {
+    *tw = shape == S2_16x4 ? 16 : (shape == S2_64x8 || shape == S2_64x16 ? 64 : 32);
+    *ty = shape == S2_16x4 || shape == S2_32x4 ? 4 : (shape == S2_32x16 || shape == S2_64x16 ? 16 : 8);
+}
+
+// The item table of the two-level launch.
 template <typename T>
 hipError_t upload_cases2(lbm_batch* B) {
     std::vector<BatchCase<T>> h(B->ncases);
-    B->nitems2 = fill_cases<T>(B->params.data(), B->layouts.data(), B->base.data(), B->ncases, 8, h.data());
+    int tw, ty;
+    step2_tile_size(B->shape2, &tw, &ty);
+    B->nitems2 = fill_cases<T>(B->params.data(), B->layouts.data(), B->base.data(), B->ncases, tw, ty, h.data());
     // one entry per item: entry w is the case of item w (k_step2_batch, PER_ITEM)
     std::vector<BatchCase<T>> items((size_t)B->nitems2);
     for (int c = 0; c < B->ncases; c++) {
@@ -327,28 +340,37 @@ void launch_batch_once(lbm_batch* B, char* state, hipStream_t s) {
     launch_batch_shape<T>(S, B->d_cases, state, s);
 }
 
-// One two-level launch over `nitems` items of a case table for 8-row tiles
-// (per_item: one entry per item, as upload_cases2 writes it; else one per case).
-template <typename T>
-void launch_batch2(int nitems, int ncases, const void* d_cases, size_t total, char* state, hipStream_t s,
-                   bool per_item) {
+// One two-level launch over `nitems` items of a table for tiles of `shape`
+// (PER_ITEM: one entry per item, as upload_cases2 writes it; else one per case).
+template <typename T, bool PER_ITEM>
+void launch_batch2(Step2Shape shape, int nitems, int ncases, const void* d_cases, size_t total, char* state,
+                   hipStream_t s) {
     const BatchCase<T>* cases = reinterpret_cast<const BatchCase<T>*>(d_cases);
     const bool nts = total > (size_t)LBM_NT_MIN_BYTES;
-    if (per_item) {
-        if (nts) k_step2_batch<T, true, true><<<nitems, dim3(TX, 8), 0, s>>>(cases, ncases, nitems, state);
-        else k_step2_batch<T, false, true><<<nitems, dim3(TX, 8), 0, s>>>(cases, ncases, nitems, state);
-    } else {
-        if (nts) k_step2_batch<T, true><<<nitems, dim3(TX, 8), 0, s>>>(cases, ncases, nitems, state);
-        else k_step2_batch<T, false><<<nitems, dim3(TX, 8), 0, s>>>(cases, ncases, nitems, state);
+    auto go = [&](auto kernel, int nt) { kernel<<<nitems, dim3(TX, nt / TX), 0, s>>>(cases, ncases, nitems, state); };
+    switch (shape) {   // the single-round shapes are far below the last-level cache
+        case S2_16x4: go(k_step2_batch<T, 16, 4, 256, false, PER_ITEM>, 256); break;
+        case S2_32x4: go(k_step2_batch<T, 32, 4, 384, false, PER_ITEM>, 384); break;
+        case S2_32x8_WIDE: go(k_step2_batch<T, 32, 8, 576, false, PER_ITEM>, 576); break;
+        case S2_32x16: go(k_step2_batch<T, 32, 16, 512, false, PER_ITEM>, 512); break;
+        case S2_32x8:
+            if (nts) go(k_step2_batch<T, 32, 8, 256, true, PER_ITEM>, 256);
+            else go(k_step2_batch<T, 32, 8, 256, false, PER_ITEM>, 256);
+            break;
+        default:
+            if constexpr (sizeof(T) == 4) {
+                if (nts) go(k_step2_batch<T, 64, 8, 512, true, PER_ITEM>, 512);
+                else go(k_step2_batch<T, 64, 8, 512, false, PER_ITEM>, 512);
+            }
     }
 }
 
 // `n` levels of the batch: two-level launches, and a one-level launch for an odd n.
 template <typename T>
 void launch_batch_levels(lbm_batch* B, char* state, int64_t n, hipStream_t s) {
-    if (B->two_level) {
+    if (B->shape2 != S2_NONE) {
         for (int64_t t = 0; t + 2 <= n; t += 2)
-            launch_batch2<T>(B->nitems2, B->ncases, B->d_cases2, B->total, state, s, true);
+            launch_batch2<T, true>(B->shape2, B->nitems2, B->ncases, B->d_cases2, B->total, state, s);
         if (n & 1) launch_batch_once<T>(B, state, s);
     } else {
         for (int64_t t = 0; t < n; t++) launch_batch_once<T>(B, state, s);
@@ -493,24 +515,55 @@ bool wide_batch(const lbm_params* cases, int ncases) {
 }
 
 // Two levels per launch: every case runs the plain Allen-Cahn step (stencil
-// gradients, present or original model) and the batch has at least 256 tiles
-// of 64 x 8 nodes, the size rule of a single lattice (lbm_step.hip).  The
-// environment variable LBM_TWO_LEVEL, read when a plan is made (and at every
-// call of the allocation-free step), overrides the size rule: "0" never, "1"
-// whatever the size.
-bool two_level_batch(const lbm_params* cases, int ncases) {
-    long long tiles8 = 0;
-    for (int c = 0; c < ncases; c++) {
-        const lbm_params& q = cases[c];
-        if (q.phase_eq != LBM_ALLEN_CAHN || q.model == LBM_MODEL_CORRECTED || q.grad_scheme != LBM_GRAD_STENCIL)
+// gradients, present or original model); LBM_TWO_LEVEL=0, read when a plan is
+// made (and at every call of the allocation-free step), turns it off.
+bool two_level_cases(const lbm_params* cases, int ncases) {
+    for (int c = 0; c < ncases; c++)
+        if (cases[c].phase_eq != LBM_ALLEN_CAHN || cases[c].model == LBM_MODEL_CORRECTED ||
+            cases[c].grad_scheme != LBM_GRAD_STENCIL)
             return false;
-        int ntx, nty;
-        tiles8 += tiles_for(q, 8, &ntx, &nty);
-    }
     const char* e = getenv("LBM_TWO_LEVEL");
-    if (e && e[0] == '0' && e[1] == 0) return false;
-    if (e && e[0] == '1' && e[1] == 0) return true;
-    return tiles8 >= 256;
+    return !(e && e[0] == '0' && e[1] == 0);
+}
+
+// What lbm_batch_levels_per_launch reports: the size rule of a single lattice,
+// at least 256 tiles of 64 x 8 nodes (LBM_TWO_LEVEL=1: whatever the size).
+bool two_level_batch(const lbm_params* cases, int ncases) {
+    if (!two_level_cases(cases, ncases)) return false;
+    long long tiles8 = 0;
+    int ntx, nty;
+    for (int c = 0; c < ncases; c++) tiles8 += tiles_for(cases[c], TX, 8, &ntx, &nty);
+    const char* e = getenv("LBM_TWO_LEVEL");
+    return (e && e[0] == '1' && e[1] == 0) || tiles8 >= 256;
+}
+
+// Tile shape of the two-level launch: the smallest that gives no CU two tiles, as
+// for a single lattice (step2_shape), else 32 x 8 tiles, two (FP64) to four (FP32)
+// workgroups of 256 threads to a CU; S2_NONE: one level per launch.  Measured on
+// MI355X, us per level, spreading cases of 128 x 64 to 512 x 256 nodes, 32x8 /
+// 64x8 / 32x16: FP32 3 cases 7.0 / 7.6 / 7.3, 8 cases 13.6 / 13.4 / 12.8, 20 cases
+// 30.1 / 31.6 / 30.6, 64 cases (streamed) 100.6 / 102.2 / 111.7; FP64 3 cases 12.1 /
+// 14.4 / 13.8, 8 cases 26.1 / 28.6 / 27.9, 64 cases 213.6 / 252.2 / 258.6.
+Step2Shape batch_shape2(const lbm_params* cases, int ncases) {
+    if (!two_level_cases(cases, ncases)) return S2_NONE;
+    bool shares = true;
+    auto fits = [&](int tw, int ty, long long limit) {
+        long long tiles = 0;
+        int ntx, nty;
+        shares = true;
+        for (int c = 0; c < ncases; c++) {
+            tiles += tiles_for(cases[c], tw, ty, &ntx, &nty);
+            shares = shares && stamp_share_ok(cases[c].nx, cases[c].ny, tw, ty);
+        }
+        return tiles <= limit && shares;
+    };
+    const long long any = 1LL << 62;
+    if (fits(16, 4, 256)) return S2_16x4;
+    if (fits(32, 4, 256)) return S2_32x4;
+    if (fits(32, 8, 256)) return S2_32x8_WIDE;
+    if (fits(32, 16, 256)) return S2_32x16;
+    if (fits(32, 8, any)) return S2_32x8;
+    return cases[0].dtype == LBM_F64 ? S2_NONE : S2_64x8;   // a case of one row
 }
 
 // ---- the batch step that allocates nothing (lbm_batch_step_noalloc) ----
@@ -569,27 +622,37 @@ int batch_step_noalloc_t(const lbm_params* cases, int ncases, char* state, int64
     hipError_t e = scratch_address(&dtab);
     if (e != hipSuccess) return hip_fail(e);
     BatchCase<T>* table = reinterpret_cast<BatchCase<T>*>(dtab);
-    // the untuned plan's shape: 8-row tiles, 64 x 4 threads (64 x 8 for the wide bodies), one
-    // workgroup per item; the same table serves the two-level launch (8-row tiles too)
-    const int ty = 8;
-    CaseChunk<T> chunk;
-    int nitems = 0;
-    for (int c0 = 0; c0 < ncases; c0 += CaseChunk<T>::N) {
-        const int cnt = ncases - c0 < CaseChunk<T>::N ? ncases - c0 : CaseChunk<T>::N;
-        memset(&chunk, 0, sizeof(chunk));
-        const int items = fill_cases<T>(cases + c0, layouts + c0, base + c0, cnt, ty, chunk.c);
-        for (int i = 0; i < cnt; i++) chunk.c[i].item_begin += nitems;
-        nitems += items;
-        chunk.first = c0;
-        chunk.count = cnt;
-        k_put_cases<T><<<1, 64, 0, s>>>(chunk, table);
-    }
-    const bool wide = wide_batch(cases, ncases);
-    const BatchShape S{ty, wide ? ty : 4, 0, nitems, ncases, wide, total};
+    auto put_cases = [&](int tw, int ty) {
+        CaseChunk<T> chunk;
+        int nitems = 0;
+        for (int c0 = 0; c0 < ncases; c0 += CaseChunk<T>::N) {
+            const int cnt = ncases - c0 < CaseChunk<T>::N ? ncases - c0 : CaseChunk<T>::N;
+            memset(&chunk, 0, sizeof(chunk));
+            const int items = fill_cases<T>(cases + c0, layouts + c0, base + c0, cnt, tw, ty, chunk.c);
+            for (int i = 0; i < cnt; i++) chunk.c[i].item_begin += nitems;
+            nitems += items;
+            chunk.first = c0;
+            chunk.count = cnt;
+            k_put_cases<T><<<1, 64, 0, s>>>(chunk, table);
+        }
+        return nitems;
+    };
     int64_t t = 0;
-    if (two_level_batch(cases, ncases))
-        for (; t + 2 <= nsteps; t += 2) launch_batch2<T>(nitems, ncases, table, total, state, s, false);
-    for (; t < nsteps; t++) launch_batch_shape<T>(S, table, state, s);
+    const Step2Shape shape = batch_shape2(cases, ncases);
+    if (shape != S2_NONE && nsteps >= 2) {
+        int tw, ty;
+        step2_tile_size(shape, &tw, &ty);
+        const int nitems = put_cases(tw, ty);
+        for (; t + 2 <= nsteps; t += 2) launch_batch2<T, false>(shape, nitems, ncases, table, total, state, s);
+    }
+    if (t < nsteps) {
+        // the untuned plan's shape: 8-row tiles, 64 x 4 threads (64 x 8 for the wide bodies), one
+        // workgroup per item
+        const int ty = 8, nitems = put_cases(TX, ty);
+        const bool wide = wide_batch(cases, ncases);
+        const BatchShape S{ty, wide ? ty : 4, 0, nitems, ncases, wide, total};
+        for (; t < nsteps; t++) launch_batch_shape<T>(S, table, state, s);
+    }
     e = hipGetLastError();
     return e == hipSuccess ? LBM_OK : hip_fail(e);
 }
@@ -637,7 +700,8 @@ int lbm_batch_create(const lbm_params* cases, int32_t ncases, int32_t autotune, 
     }
     hipError_t e = B->dtype == LBM_F32 ? upload_cases<float>(B, B->ty) : upload_cases<double>(B, B->ty);
     B->two_level = two_level_batch(cases, ncases);
-    if (e == hipSuccess && B->two_level) e = B->dtype == LBM_F32 ? upload_cases2<float>(B) : upload_cases2<double>(B);
+    B->shape2 = batch_shape2(cases, ncases);
+    if (e == hipSuccess && B->shape2 != S2_NONE) e = B->dtype == LBM_F32 ? upload_cases2<float>(B) : upload_cases2<double>(B);
     if (e != hipSuccess) {
         lbm_batch_destroy(B);
         return hip_fail(e);

@@ -30,6 +30,13 @@ __device__ __forceinline__ void xcd_tile(int b, int ntx, int nty, int& xt, int& 
     yt = t / ntx;
 }
 
+// Workgroup b of n, dealt to the XCDs in contiguous bands of 0 .. n - 1.
+__device__ __forceinline__ int xcd_band(int b, int n) {
+    constexpr int NX = 8;
+    const int q = n / NX, rem = n % NX, xcd = b % NX, slot = b / NX;
+    return xcd < rem ? xcd * (q + 1) + slot : rem * (q + 1) + (xcd - rem) * q + slot;
+}
+
 template <typename T, typename OFF>
 __device__ __forceinline__ T ld(const char* base, OFF byteoff) {
     return *reinterpret_cast<const T*>(base + byteoff);

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(NT) void k_step2(KParams<T> P, char* state, size_t 
     int xt, yt;
     xcd_tile(blockIdx.x, ntx, nty, xt, yt);
     step2_body<T, TW, TY, NT, STD, NTS, false, LOCAL>(
-        (ParamsPtr<T>)__builtin_amdgcn_kernarg_segment_ptr(),
+        kernel_params<step2_reload<T>(TW, TY, NT)>(P),
         StateTile{state, off0, off1, off_stamp, sh, (int)blockIdx.x, xt, yt, 0}, L);
 }
 

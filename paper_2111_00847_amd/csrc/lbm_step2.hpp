@@ -69,6 +69,17 @@ struct Step2Lds {
     T mxa[LOCAL ? NA : 1], mya[LOCAL ? NA : 1];
 };
 
+// Whether the body reads its parameters anew in each phase (params_at): in FP64,
+// where held from end to end they spilled into vector lanes (240 of the 2900
+// vector instructions; 1999 x 2203: 237 to 228 us per level), and in the FP32 tiles
+// of large lattices (64 x 8: 4096 x 4096 362 to 357 us, 2048 x 2048 local gradient
+// 112 to 104; 32 x 8: a batch of 64 cases 100.6 to 97.3).  A small lattice's single
+// round of tiles gains more from having them at hand (64 x 64 FP32 3.3 to 3.1 us).
+template <typename T>
+__host__ __device__ constexpr bool step2_reload(int tw, int ty, int nt) {
+    return sizeof(T) == 8 || (ty == 8 && nt == tw * ty);
+}
+
 // Two levels of one TW x TY tile, with the LDS `L` of the workgroup of NT
 // threads (64 x NT/64).  `tile` (StateTile, TapeTile) says which tile, where its
 // level is read and where level + 2 goes.  MID also stores the tile's
@@ -93,7 +104,7 @@ struct Step2Lds {
 // nodes store their reflected populations at the positions beyond the wall
 // that B pulls from.
 template <typename T, int TW, int TY, int NT, bool STD, bool NTS, bool MID = false, bool LOCAL = false, typename Tile>
-__device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2Lds<T, TW, TY, LOCAL>& L) {
+__device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(TW, TY, NT)> params, Tile tile, Step2Lds<T, TW, TY, LOCAL>& L) {
     using Lds = Step2Lds<T, TW, TY, LOCAL>;
     static_assert(!(LOCAL && (MID || STD)), "the local scheme: no tape, general collision");
     constexpr int AW = Lds::AW, AH = Lds::AH, WW = Lds::WW, WH = Lds::WH, NW = Lds::NW, GW = Lds::GW, GH = Lds::GH;
@@ -102,7 +113,7 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
     static_assert(NRING1 <= NT && TW * TY <= NT, "one node and one window ring position per thread");
     constexpr uint32_t ES = sizeof(T);
 
-    const KParams<T> P = params_at<T>(params);   // the lattice (the model's constants are read below)
+    const KParams<T>& P = params_at<T>(params);   // the lattice (the model's constants are read below)
     const int tid = threadIdx.y * TX + threadIdx.x;
     const int x0 = tile.xt * TW, y0 = tile.yt * TY;
     const uint32_t plB = (uint32_t)P.plane * ES;   // bytes of a plane
@@ -175,7 +186,7 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
         int wx, wy;
         window_pos(s, wx, wy);
         if (!ok[s] || !in_region(wx, wy)) continue;
-        const KParams<T> P = params_at<T>(params);
+        const KParams<T>& P = params_at<T>(params);
         const int ax = wx - 1, ay = wy - 1;
         const int idx = tid + s * NT - (WW - AW) * wy - (AW + 1);   // ay * AW + ax
         T gx, gy, lap, gxp = T(0), gyp = T(0), lp, php = T(0), up = T(0), vp = T(0);
@@ -288,7 +299,7 @@ __device__ __forceinline__ void step2_body(ParamsPtr<T> params, Tile tile, Step2
 
     // ---- B: the step of level n + 1 on the tile, stored into the other copy
     if ((NT == TW * TY || tid < TW * TY) && (inner || (x < P.nx && y < P.ny))) {
-        const KParams<T> P = params_at<T>(params);
+        const KParams<T>& P = params_at<T>(params);
         T gb[9];
 #pragma unroll
         for (int i = 0; i < Q; i++) gb[i] = L.ga[i][c - cy(i) * AW - cx(i)];

@@ -46,3 +46,38 @@ def test_shape_equals_one_level_launches(size, dtype, grad):
     assert sa["step"] == sb["step"] == 6
     for k in ("f", "g", "hist"):
         assert torch.equal(sa[k], sb[k]), (k, float((sa[k] - sb[k]).abs().max()))
+
+
+BATCHES = {   # sizes of the cases -> the shape the rule takes for the batch
+    "16x4": [(40, 32), (64, 64), (70, 40)], "32x4 (a case short of stamps)": [(61, 9), (128, 64), (40, 33)],
+    "32x8, one round": [(256, 120), (130, 75)], "32x16, one round": [(250, 250), (130, 75), (5, 8)],
+    "32x8": [(512, 256)] * 3 + [(130, 75), (2, 2)], "32x8 streamed": [(1024, 1024), (900, 1030), (37, 41)],
+    "64x8 / one level": [(17000, 1), (70, 9)],
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape", list(BATCHES))
+def test_batch_shape_equals_lone_one_level_runs(shape, dtype):
+    """Every case of a batch, seven levels on (an odd tail), against lone one-level
+    runs; and the allocation-free step, which writes its own tables."""
+    from paper_2111_00847_amd import api
+    from paper_2111_00847_amd.sim import BatchSim, Sim
+    cases = [W.Case(nx=nx, ny=ny, wall_y=ny > 1, rhoA=20.0, nuA=0.05, nuB=0.2, sigma=0.01, M=0.05, dtype=dtype,
+                    theta=(1.2, 1.9, 0.7, 2.4)) for nx, ny in BATCHES[shape]]
+    phis = [W.random_state_fields(c, seed=k)[0] for k, c in enumerate(cases)]
+    print(shape, dtype, flush=True)
+    a, b = BatchSim(cases).init(phis), BatchSim(cases).init(phis)
+    a.step(7)
+    api.lbm_batch_step_noalloc(b.params, b.state, 7)
+    os.environ["LBM_TWO_LEVEL"] = "0"
+    try:
+        for k, c in enumerate(cases):
+            want = Sim(c).init(phis[k]).step(7).export_state()
+            for batch in (a, b):
+                got = batch.case(k).export_state()
+                assert got["step"] == 7
+                for q in ("f", "g", "hist"):
+                    assert torch.equal(got[q], want[q]), (k, q)
+    finally:
+        os.environ.pop("LBM_TWO_LEVEL", None)
