@@ -235,7 +235,7 @@ __global__ __launch_bounds__(NT) void k_tape_step2(KParams<T> P, char* tape, siz
     char* src = tape + TAPE_HDR + (size_t)j * slot;
     int xt, yt;
     xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_body<T, TW, TY, NT, STD, NTS, true>(kernel_params<step2_reload<T>(TW, TY, NT)>(P),
+    step2_body<T, TW, TY, NT, STD, NTS ? ST_NT : ST_THROUGH, true>(kernel_params<step2_reload<T>(TW, TY, NT)>(P),
                                               TapeTile{src, src + slot, src + 2 * slot, n, xt, yt}, L);
 }
 

@@ -117,8 +117,8 @@ __global__ __launch_bounds__(NT) void k_step2_batch(const BatchCase<T>* __restri
     const StateTile tile{batch_state + C.base, C.off0, C.off1, C.off_stamp, C.share, local, local % C.ntx,
                          local / C.ntx, 0};
     auto body = [&](auto params) {
-        if (C.P.rates_std) step2_body<T, TW, TY, NT, true, NTS>(params, tile, L);
-        else step2_body<T, TW, TY, NT, false, NTS>(params, tile, L);
+        if (C.P.rates_std) step2_body<T, TW, TY, NT, true, NTS ? ST_NT : ST_THROUGH>(params, tile, L);
+        else step2_body<T, TW, TY, NT, false, NTS ? ST_NT : ST_THROUGH>(params, tile, L);
     };
     body(memory_params<step2_reload<T>(TW, TY, NT)>(C.P));
 }

@@ -10,9 +10,10 @@ namespace lbm {
 template <typename T>
 hipError_t launch_step(const KParams<T>& P, char* state, const Layout& L, int64_t nsteps, hipStream_t s,
                        int ty, int by, int& copy);
-// two levels of the plain Allen-Cahn step in one launch (lbm_step2.hip)
+// two levels of the plain Allen-Cahn step in one launch (lbm_step2.hip); back: the
+// tile rows from last to first (xcd_tile)
 template <typename T>
-void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s);
+void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, bool back);
 // A tile of the two-level launch owns at least one level stamp (lbm_step2.hpp).
 inline bool stamp_share_ok(int nx, int ny, int tw, int ty) {
     const long long nstamp = (long long)((nx + STAMP_BAND - 1) / STAMP_BAND) * ny;
@@ -75,7 +76,8 @@ hipError_t launch_export(const KParams<T>& P, const char* state, const Layout& L
                          hipStream_t s);
 // the Allen-Cahn step / moments with the local gradient scheme (lbm_local.hip)
 template <typename T, int MODE>
-void launch_local(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p);
+void launch_local(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                  bool back = false);
 template <typename T>
 hipError_t launch_diagnostics(const KParams<T>& P, const char* state, const Layout& L, double* host_out,
                               hipStream_t s);

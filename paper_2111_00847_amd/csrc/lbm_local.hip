@@ -24,11 +24,11 @@ constexpr int LOC_NBY = LBM_LOC_NBY;
 template <typename T, int MODE, bool NT = true, typename OFF = uint64_t>
 __global__ __launch_bounds__(TX* LOC_NBY) void k_step_local(KParams<T> P, char* state, size_t off0, size_t off1,
                                                       size_t off_stamp, int ntx, int nty, T* out_phi, T* out_u,
-                                                      T* out_p) {
+                                                      T* out_p, bool back) {
     __shared__ T sphi[LOC_TY + 2][TX + 3];
     int xt, yt;
     if (LBM_XCD_REMAP) {
-        xcd_tile(blockIdx.x, ntx, nty, xt, yt);
+        xcd_tile(blockIdx.x, ntx, nty, xt, yt, back);
     } else {
         xt = blockIdx.x % ntx;
         yt = blockIdx.x / ntx;
@@ -42,26 +42,28 @@ __global__ __launch_bounds__(TX* LOC_NBY) void k_step_local(KParams<T> P, char* 
 // 6.21 against 7.84, 1024 x 512 20.3 against 22.4, 4096 x 4096 582 either way);
 // moments and larger copies with 64-bit ones.
 template <typename T, int MODE>
-void launch_local(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p) {
+void launch_local(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                  bool back) {
     const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + LOC_TY - 1) / LOC_TY;
     const dim3 grd(ntx * nty), blk(TX, LOC_NBY);
     const bool small = L.buf_bytes < (size_t(1) << 32);
-    if (MODE == 0 && cached_state(L))
+    if (MODE == 0 && small && plain_stores(L, P.nx))
         k_step_local<T, MODE, false, uint32_t><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp,
-                                                                  ntx, nty, phi, u, p);
+                                                                  ntx, nty, phi, u, p, back);
     else if (MODE == 0 && small)
         k_step_local<T, MODE, true, uint32_t><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp,
-                                                                 ntx, nty, phi, u, p);
+                                                                 ntx, nty, phi, u, p, back);
     else
         k_step_local<T, MODE><<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi,
-                                                  u, p);
+                                                  u, p, back);
 }
 
-template void launch_local<float, 0>(const KParams<float>&, char*, const Layout&, hipStream_t, float*, float*, float*);
-template void launch_local<float, 1>(const KParams<float>&, char*, const Layout&, hipStream_t, float*, float*, float*);
-template void launch_local<double, 0>(const KParams<double>&, char*, const Layout&, hipStream_t, double*, double*,
-                                      double*);
-template void launch_local<double, 1>(const KParams<double>&, char*, const Layout&, hipStream_t, double*, double*,
-                                      double*);
+#define LBM_INSTANTIATE(T, MODE) \
+    template void launch_local<T, MODE>(const KParams<T>&, char*, const Layout&, hipStream_t, T*, T*, T*, bool);
+LBM_INSTANTIATE(float, 0)
+LBM_INSTANTIATE(float, 1)
+LBM_INSTANTIATE(double, 0)
+LBM_INSTANTIATE(double, 1)
+#undef LBM_INSTANTIATE
 
 }  // namespace lbm

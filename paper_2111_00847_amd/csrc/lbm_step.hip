@@ -26,19 +26,21 @@
 
 namespace lbm {
 
-// Steps on states that the last-level cache holds (NT false) start their loads
+// Steps on states that the last-level cache holds (HINT) start their loads
 // on the copy of the host's parity guess `hint` while the level stamp is read
 // (step_core); LBM_PARITY_HINT=0 reads the stamp first there too.  States
 // streamed from HBM always read the stamp first: a wrong guess would cost a
 // whole extra copy of HBM reads (the guess is wrong after every replay of a
 // captured graph of an odd number of launches, 1.5x the step time measured on
 // 4096 x 4096 FP32), while the stamp read costs a tile little next to its
-// stream of loads.
+// stream of loads; there the guess only sets the direction of the sweep
+// (xcd_tile).
 #ifndef LBM_PARITY_HINT
 #define LBM_PARITY_HINT 1
 #endif
 
-template <typename T, int TY, int MODE, typename OFF, int NBY, bool STD, bool NT = true, bool LATE_G = false>
+template <typename T, int TY, int MODE, typename OFF, int NBY, bool STD, bool NT = true, bool LATE_G = false,
+          bool HINT = MODE == 0 && LBM_PARITY_HINT && !NT>
 __global__ __launch_bounds__(TX* NBY) __attribute__((amdgpu_waves_per_eu(StepWaves<T, TY, NBY>::value)))
 void k_step(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stamp, int ntx, int nty, T* out_phi,
             T* out_u, T* out_p, int hint) {
@@ -46,12 +48,12 @@ void k_step(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stam
     __shared__ T sphp[TY + 2][TX + 3];
     int xt, yt;
     if (LBM_XCD_REMAP) {
-        xcd_tile(blockIdx.x, ntx, nty, xt, yt);
+        xcd_tile(blockIdx.x, ntx, nty, xt, yt, MODE == 0 && !HINT && hint != 0);
     } else {
         xt = blockIdx.x % ntx;
         yt = blockIdx.x / ntx;
     }
-    step_tile<T, TY, MODE, OFF, NBY, STD, NT, LATE_G, MODE == 0 && LBM_PARITY_HINT && !NT>(
+    step_tile<T, TY, MODE, OFF, NBY, STD, NT, LATE_G, HINT>(
         P, state, off0, off1, off_stamp, xt, yt, out_phi, out_u, out_p, sphi, sphp, hint);
 }
 
@@ -73,11 +75,11 @@ void k_step(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stam
 template <typename T, int TY, int MODE, bool ACC, bool STD, bool NT = true, int NBY = BY, typename OFF = uint64_t>
 __global__ __launch_bounds__(TX* NBY) void k_step_ch(KParams<T> P, char* state, size_t off0, size_t off1,
                                                     size_t off_stamp, int ntx, int nty, T* out_phi, T* out_u,
-                                                    T* out_p) {
+                                                    T* out_p, bool back) {
     __shared__ ChWindow<T, TY> W;
     int xt, yt;
     if (LBM_XCD_REMAP) {
-        xcd_tile(blockIdx.x, ntx, nty, xt, yt);
+        xcd_tile(blockIdx.x, ntx, nty, xt, yt, back);
     } else {
         xt = blockIdx.x % ntx;
         yt = blockIdx.x / ntx;
@@ -91,10 +93,11 @@ constexpr int CH_TY = (LBM_CH_TY == 4 || LBM_CH_TY == 16) ? LBM_CH_TY : 8;
 constexpr int CH_NBY = CH_TY == 4 ? 4 : 8;
 
 template <typename T, int MODE, bool ACC, bool STD, bool NT, typename OFF>
-static void launch_ch_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p) {
+static void launch_ch_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                            bool back) {
     const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + CH_TY - 1) / CH_TY;
     k_step_ch<T, CH_TY, MODE, ACC, STD, NT, CH_NBY, OFF><<<ntx * nty, dim3(TX, CH_NBY), 0, s>>>(
-        P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p);
+        P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p, back);
 }
 
 // Steps address a copy below 4 GiB with 32-bit byte offsets from a uniform
@@ -103,39 +106,43 @@ static void launch_ch_shape(const KParams<T>& P, char* state, const Layout& L, h
 // per step: 554 against 571 at 4096^2, 37.0 against 39.7 at 1024^2, 7.0 against
 // 9.6 at 200^2); moments and larger copies with 64-bit ones.
 template <typename T, int MODE, bool ACC, bool STD, bool NT = true>
-static void launch_ch_acc_std(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p) {
+static void launch_ch_acc_std(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                              bool back) {
     if constexpr (MODE == 0) {
         if (L.buf_bytes < (size_t(1) << 32)) {
-            launch_ch_shape<T, MODE, ACC, STD, NT, uint32_t>(P, state, L, s, phi, u, p);
+            launch_ch_shape<T, MODE, ACC, STD, NT, uint32_t>(P, state, L, s, phi, u, p, back);
             return;
         }
     }
-    launch_ch_shape<T, MODE, ACC, STD, NT, uint64_t>(P, state, L, s, phi, u, p);
+    launch_ch_shape<T, MODE, ACC, STD, NT, uint64_t>(P, state, L, s, phi, u, p, back);
 }
 
 // the standard rates compiled in for steps (moments do not collide); steps on
-// a state that the last-level cache holds store it with ordinary stores
+// a state that the last-level cache holds, or of rows that end inside a cache
+// line (whole_lines), store it with ordinary stores
 template <typename T, int MODE, bool ACC>
-static void launch_ch_acc(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p) {
+static void launch_ch_acc(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                          bool back) {
     if constexpr (MODE == 0) {
-        const bool cached = cached_state(L);
+        const bool plain = plain_stores(L, P.nx);
         if (P.rates_std) {
-            if (cached) launch_ch_acc_std<T, MODE, ACC, true, false>(P, state, L, s, phi, u, p);
-            else launch_ch_acc_std<T, MODE, ACC, true>(P, state, L, s, phi, u, p);
+            if (plain) launch_ch_acc_std<T, MODE, ACC, true, false>(P, state, L, s, phi, u, p, back);
+            else launch_ch_acc_std<T, MODE, ACC, true>(P, state, L, s, phi, u, p, back);
         } else {
-            if (cached) launch_ch_acc_std<T, MODE, ACC, false, false>(P, state, L, s, phi, u, p);
-            else launch_ch_acc_std<T, MODE, ACC, false>(P, state, L, s, phi, u, p);
+            if (plain) launch_ch_acc_std<T, MODE, ACC, false, false>(P, state, L, s, phi, u, p, back);
+            else launch_ch_acc_std<T, MODE, ACC, false>(P, state, L, s, phi, u, p, back);
         }
     } else {
-        launch_ch_acc_std<T, MODE, ACC, false>(P, state, L, s, phi, u, p);
+        launch_ch_acc_std<T, MODE, ACC, false>(P, state, L, s, phi, u, p, back);
     }
 }
 
 // CH (any model) or the corrected AC model: the two-node-window kernels.
 template <typename T, int MODE>
-static void launch_ch(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p) {
-    if (P.pf == 1) launch_ch_acc<T, MODE, false>(P, state, L, s, phi, u, p);
-    else launch_ch_acc<T, MODE, true>(P, state, L, s, phi, u, p);
+static void launch_ch(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
+                      bool back = false) {
+    if (P.pf == 1) launch_ch_acc<T, MODE, false>(P, state, L, s, phi, u, p, back);
+    else launch_ch_acc<T, MODE, true>(P, state, L, s, phi, u, p, back);
 }
 
 // ---------------------------------------------------------------- init / import / export
@@ -579,6 +586,13 @@ static void launch_tile(const KParams<T>& P, char* state, const Layout& L, hipSt
         else
             k_step<T, TY, MODE, uint32_t, NBY, false, false><<<ntx * nty, blk, 0, s>>>(
                 P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p, hint);
+    } else if (MODE == 0 && small_copy(L) && !whole_lines(L, P.nx)) {
+        if (std_rates)
+            k_step<T, TY, MODE, uint32_t, NBY, true, false, false, false><<<ntx * nty, blk, 0, s>>>(
+                P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p, hint);
+        else
+            k_step<T, TY, MODE, uint32_t, NBY, false, false, false, false><<<ntx * nty, blk, 0, s>>>(
+                P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p, hint);
     } else if (small_copy(L)) {
         if (std_rates)
             k_step<T, TY, MODE, uint32_t, NBY, true><<<ntx * nty, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1],
@@ -633,16 +647,18 @@ template <typename T>
 hipError_t launch_step(const KParams<T>& P, char* state, const Layout& L, int64_t nsteps, hipStream_t s,
                        int ty, int by, int& copy) {
     constexpr int T16 = sizeof(T) == 8 ? 8 : 16;   // FP64 tiles stop at 8 rows
+    auto back = [&] { return copy != 0 && !cached_state(L); };   // alternate sweeps (xcd_tile)
     if (two_level_step(L, P.nx, P.ny, P.pf, P.model))
         for (; nsteps >= 2; nsteps -= 2) {
-            launch_step2<T>(P, state, L, s);
+            launch_step2<T>(P, state, L, s, back());
             copy ^= 1;
         }
     for (int64_t t = 0; t < nsteps; t++) {
         const int h = copy;   // the copy this launch is expected to find the state in
+        const bool rev = back();
         copy ^= 1;
-        if (P.pf == 1 || P.model == 2) launch_ch<T, 0>(P, state, L, s, nullptr, nullptr, nullptr);
-        else if (P.grad == 1) launch_local<T, 0>(P, state, L, s, nullptr, nullptr, nullptr);
+        if (P.pf == 1 || P.model == 2) launch_ch<T, 0>(P, state, L, s, nullptr, nullptr, nullptr, rev);
+        else if (P.grad == 1) launch_local<T, 0>(P, state, L, s, nullptr, nullptr, nullptr, rev);
         else if (ty == 4) launch_tile<T, 4, 0>(P, state, L, s, nullptr, nullptr, nullptr, h);
         else if (ty == 8 || sizeof(T) == 8) {
             if (by == 8) launch_tile<T, 8, 0, 8>(P, state, L, s, nullptr, nullptr, nullptr, h);

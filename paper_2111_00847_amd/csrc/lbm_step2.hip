@@ -20,8 +20,9 @@
 // of this launch equal two one-level launches bit for bit.  The ring costs
 // recomputation (the region of A is (TW + 4)(TY + 4) nodes) and L2 reads of
 // the neighbouring tiles' rows, not HBM traffic beyond those rows: a launch
-// reads the state once and writes it once for two levels.  Stores bypass the
-// caches (non-temporal) on states larger than the last-level cache.
+// reads the state once and writes it once for two levels.  On states larger than
+// the last-level cache the sweeps alternate in direction (xcd_tile) and rows of
+// whole cache lines are stored non-temporally (whole_lines).
 //
 // Where the time of a launch goes (wave clocks, 256 x 1024 FP32, 64 x 16 tiles, one
 // per CU, before the window's ring was read with the region and the stores wrote
@@ -39,50 +40,55 @@ namespace lbm {
 // P is the kernel's first argument: the body reads it from the argument
 // segment.  LOCAL: the local gradient scheme (Eq. local; the general collision,
 // as the one-level kernel runs it).
-template <typename T, int TW, int TY, int NT, bool STD, bool NTS, bool LOCAL>
+template <typename T, int TW, int TY, int NT, bool STD, StoreKind SK, bool LOCAL>
 __global__ __launch_bounds__(NT) void k_step2(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stamp,
-                                              int ntx, int nty, StampShare sh) {
+                                              int ntx, int nty, StampShare sh, bool back) {
     __shared__ Step2Lds<T, TW, TY, LOCAL> L;
     int xt, yt;
-    xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_body<T, TW, TY, NT, STD, NTS, false, LOCAL>(
+    xcd_tile(blockIdx.x, ntx, nty, xt, yt, back);
+    step2_body<T, TW, TY, NT, STD, SK, false, LOCAL>(
         kernel_params<step2_reload<T>(TW, TY, NT)>(P),
         StateTile{state, off0, off1, off_stamp, sh, (int)blockIdx.x, xt, yt, 0}, L);
 }
 
 template <typename T, int TW, int TY, int NT>
-static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
+static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, bool back) {
     const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
     const StampShare sh = stamp_share((long long)L.nstamp, (long long)ntx * nty);
     const dim3 grd(ntx * nty), blk(TX, NT / TX);
     auto go = [&](auto kernel) {
-        kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh);
+        kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh, back);
     };
-    // the one-level step's store policy: ordinary stores while both copies fit the cache
-    const bool cached = cached_state(L);
-    if (P.grad == 1) cached ? go(k_step2<T, TW, TY, NT, false, false, true>) : go(k_step2<T, TW, TY, NT, false, true, true>);
-    else if (P.rates_std) cached ? go(k_step2<T, TW, TY, NT, true, false, false>) : go(k_step2<T, TW, TY, NT, true, true, false>);
-    else cached ? go(k_step2<T, TW, TY, NT, false, false, false>) : go(k_step2<T, TW, TY, NT, false, true, false>);
+    // written through while the cache holds both copies, else the streamed store kind
+    auto by_store = [&](auto kind) {
+        constexpr StoreKind SK = decltype(kind)::value;
+        if (P.grad == 1) go(k_step2<T, TW, TY, NT, false, SK, true>);
+        else if (P.rates_std) go(k_step2<T, TW, TY, NT, true, SK, false>);
+        else go(k_step2<T, TW, TY, NT, false, SK, false>);
+    };
+    if (cached_state(L)) by_store(std::integral_constant<StoreKind, ST_THROUGH>());
+    else if (whole_lines(L, P.nx)) by_store(std::integral_constant<StoreKind, ST_NT>());
+    else by_store(std::integral_constant<StoreKind, ST_PLAIN>());
 }
 
 // The launch's tiles (step2_shape).
 template <typename T>
-void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s) {
+void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, bool back) {
     switch (step2_shape(P.nx, P.ny, sizeof(T), cached_state(L))) {
-        case S2_16x4: launch_step2_shape<T, 16, 4, 256>(P, state, L, s); break;
-        case S2_32x4: launch_step2_shape<T, 32, 4, 384>(P, state, L, s); break;
-        case S2_32x8_WIDE: launch_step2_shape<T, 32, 8, 576>(P, state, L, s); break;
-        case S2_32x16: launch_step2_shape<T, 32, 16, 512>(P, state, L, s); break;
+        case S2_16x4: launch_step2_shape<T, 16, 4, 256>(P, state, L, s, back); break;
+        case S2_32x4: launch_step2_shape<T, 32, 4, 384>(P, state, L, s, back); break;
+        case S2_32x8_WIDE: launch_step2_shape<T, 32, 8, 576>(P, state, L, s, back); break;
+        case S2_32x16: launch_step2_shape<T, 32, 16, 512>(P, state, L, s, back); break;
         case S2_64x16:
-            if constexpr (sizeof(T) == 4) launch_step2_shape<T, 64, 16, 1024>(P, state, L, s);
+            if constexpr (sizeof(T) == 4) launch_step2_shape<T, 64, 16, 1024>(P, state, L, s, back);
             break;
         default:
-            if constexpr (sizeof(T) == 8) launch_step2_shape<T, 32, 8, 256>(P, state, L, s);
-            else launch_step2_shape<T, 64, 8, 512>(P, state, L, s);
+            if constexpr (sizeof(T) == 8) launch_step2_shape<T, 32, 8, 256>(P, state, L, s, back);
+            else launch_step2_shape<T, 64, 8, 512>(P, state, L, s, back);
     }
 }
 
-template void launch_step2<float>(const KParams<float>&, char*, const Layout&, hipStream_t);
-template void launch_step2<double>(const KParams<double>&, char*, const Layout&, hipStream_t);
+template void launch_step2<float>(const KParams<float>&, char*, const Layout&, hipStream_t, bool);
+template void launch_step2<double>(const KParams<double>&, char*, const Layout&, hipStream_t, bool);
 
 }  // namespace lbm

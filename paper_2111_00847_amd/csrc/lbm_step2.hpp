@@ -103,7 +103,7 @@ __host__ __device__ constexpr bool step2_reload(int tw, int ty, int nt) {
 // the region: the same cache lines.  Bounce-back costs B nothing: A's wall
 // nodes store their reflected populations at the positions beyond the wall
 // that B pulls from.
-template <typename T, int TW, int TY, int NT, bool STD, bool NTS, bool MID = false, bool LOCAL = false, typename Tile>
+template <typename T, int TW, int TY, int NT, bool STD, StoreKind SK, bool MID = false, bool LOCAL = false, typename Tile>
 __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(TW, TY, NT)> params, Tile tile, Step2Lds<T, TW, TY, LOCAL>& L) {
     using Lds = Step2Lds<T, TW, TY, LOCAL>;
     static_assert(!(LOCAL && (MID || STD)), "the local scheme: no tape, general collision");
@@ -322,17 +322,17 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
         collide_g<T, STD>(P, M, gb);
         const uint32_t k = ((uint32_t)y * (uint32_t)P.nx + (uint32_t)x) * ES;
         const CopyAddr<uint32_t> db(tile.dst(), bytes);
-        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 0, rest_encode<T>(f0n, M.phi, P.rest_w));
+        db.template st<SK>(k, 0, rest_encode<T>(f0n, M.phi, P.rest_w));
 #pragma unroll
-        for (int i = 1; i < Q; i++) db.template st<NTS ? ST_NT : ST_THROUGH>(k, i * plB, fb[i]);
+        for (int i = 1; i < Q; i++) db.template st<SK>(k, i * plB, fb[i]);
 #pragma unroll
-        for (int i = 0; i < Q; i++) db.template st<NTS ? ST_NT : ST_THROUGH>(k, (9 + i) * plB, gb[i]);
-        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 18 * plB, M.phi);
-        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 19 * plB, M.u);
-        db.template st<NTS ? ST_NT : ST_THROUGH>(k, 20 * plB, M.v);
+        for (int i = 0; i < Q; i++) db.template st<SK>(k, (9 + i) * plB, gb[i]);
+        db.template st<SK>(k, 18 * plB, M.phi);
+        db.template st<SK>(k, 19 * plB, M.u);
+        db.template st<SK>(k, 20 * plB, M.v);
         if constexpr (LOCAL) {
-            db.template st<NTS ? ST_NT : ST_THROUGH>(k, 21 * plB, M.mx);
-            db.template st<NTS ? ST_NT : ST_THROUGH>(k, 22 * plB, M.my);
+            db.template st<SK>(k, 21 * plB, M.mx);
+            db.template st<SK>(k, 22 * plB, M.my);
         }
     }
     // every wave read the stamp before the barriers above

@@ -72,3 +72,20 @@ def test_init_export_import(size, dtype, kind):
     assert torch.equal(e["f"][1:], d["f"][1:])
     # f_0 is stored relative to the history phi: one rounding of its type
     assert float((e["f"][0] - d["f"][0]).abs().max()) <= (0.0 if dtype == "f64" else 1.2e-7)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("size", [(1023, 40), (1025, 20), (2000, 300), (4100, 33)], ids=lambda s: f"{s[0]}x{s[1]}")
+def test_hydrostatic_pressure_in_place_has_the_same_bits(size, dtype):
+    """A p0 that is phi0 itself runs in one workgroup, another array in staged
+    columns: the same additions in the same order, the mean's included (wider
+    than its 1024 threads too), so the same bits."""
+    from paper_2111_00847_amd import api
+    nx, ny = size
+    p = api.make_params(W.Case(nx=nx, ny=ny, rhoA=1000.0, gravity=(0.0, -1e-3), rho_ref=2.0, dtype=dtype))
+    gen = torch.Generator().manual_seed(nx)
+    t = torch.rand((ny, nx), generator=gen, dtype=torch.float64).to("cuda", torch.float64 if dtype == "f64" else torch.float32)
+    out = torch.empty_like(t)
+    api.lbm_hydrostatic_pressure(p, t, out)
+    api.lbm_hydrostatic_pressure(p, t, t)
+    assert torch.equal(out, t), float((out - t).abs().max())

@@ -9,6 +9,7 @@ one-level launches.
 """
 import os
 
+import numpy as np
 import pytest
 
 import workloads as W
@@ -81,3 +82,34 @@ def test_batch_shape_equals_lone_one_level_runs(shape, dtype):
                     assert torch.equal(got[q], want[q]), (k, q)
     finally:
         os.environ.pop("LBM_TWO_LEVEL", None)
+
+
+MODELS = {"stencil": {}, "local": {"grad_scheme": "local"}, "corrected": {"model": "corrected"}, "ch": {}}
+
+
+@pytest.mark.parametrize("size", [(2050, 400, 3, "f32"), (2048, 400, 3, "f32"), (1030, 400, 3, "f64"), (1024, 400, 3, "f64")],
+                         ids=lambda s: f"{s[0]}x{s[1]}x{s[2]}_{s[3]}")
+@pytest.mark.parametrize("model", list(MODELS))
+def test_streamed_state_equals_its_cached_period(model, size):
+    """A periodic lattice that is a smaller one repeated in y stays its copies, bit
+    for bit: the smaller state fits the last-level cache (written through, swept
+    forward), the larger one is streamed (swept forward and back by turns, stored
+    non-temporally where its rows are whole cache lines).  Five levels in one call,
+    then one, then two, so that launches of one and of two levels run both ways."""
+    from paper_2111_00847_amd.sim import Sim
+    nx, ny, k, dtype = size
+    case = W.Case(nx=nx, ny=ny, rhoA=20.0, nuA=0.05, nuB=0.2, sigma=0.01, M=0.05, body_force=(1e-6, -2e-6),
+                  rho_ref=3.0, dtype=dtype, **MODELS[model])
+    phi0, u0, p0 = W.random_state_fields(case, seed=nx)
+    if model == "ch":
+        case, phi0 = W.to_cahn_hilliard(case, phi0)
+    big = case.replace(ny=k * ny)
+    rep = lambda a: np.concatenate([a] * k, axis=-2)
+    a, b = Sim(case).init(phi0, u0, p0), Sim(big).init(rep(phi0), rep(u0), rep(p0))
+    for n in (5, 1, 2):
+        a.step(n)
+        b.step(n)
+        sa, sb = a.export_state(), b.export_state()
+        for name in ("f", "g", "hist"):
+            for i in range(k):
+                assert torch.equal(sa[name], sb[name][:, i * ny:(i + 1) * ny]), (name, n, i)
