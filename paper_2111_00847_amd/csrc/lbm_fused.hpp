@@ -13,18 +13,22 @@ namespace lbm {
 // vertical strip of columns [j ntx/8, (j+1) ntx/8) and walks it row by row
 // (the tile above a tile was processed ntx/8 tiles earlier, so the shared halo
 // row is still in that XCD's L2); otherwise XCD j takes a contiguous band of
-// tiles in row-major order.  `back` walks the rows from the last to the first: a
+// tiles in row-major order, also for the two-level launch on a state that the
+// last-level cache holds (`strips` false: us per level, bands against strips, FP32
+// 512 x 1024 12.5 / 14.7, 1024 x 512 12.8 / 13.4, 1024 x 1024 22.5 / 24.5, local
+// gradient 24.0 / 25.8, FP64 1024 x 700 32.5 / 33.6; streamed 3072 x 2000 143 / 137).
+// `back` walks the rows from the last to the first: a
 // state larger than the last-level cache is swept forward and back by turns, so
 // that a launch begins with the rows that the launch before it left in that
 // cache (us per level against always forward: FP32 2704 x 2213 139.9 against
 // 146.6, 2200 x 2000 100.0 / 105.9, 3000 x 3000 202.1 / 210.1, 4000 x 4100 373 /
 // 383, FP64 1500 x 1500 98.7 / 101.1, Cahn-Hilliard 1601 x 1601 105 / 116).
 // Returns (xt, yt).
-__device__ __forceinline__ void xcd_tile(int b, int ntx, int nty, int& xt, int& yt, bool back = false) {
+__device__ __forceinline__ void xcd_tile(int b, int ntx, int nty, int& xt, int& yt, bool back = false, bool strips = true) {
     constexpr int NX = 8;
     const int nb = ntx * nty;
     const int xcd = b % NX, slot = b / NX;
-    if (ntx % NX == 0 && ntx >= 2 * NX) {
+    if (strips && ntx % NX == 0 && ntx >= 2 * NX) {
         const int sw = ntx / NX;
         xt = xcd * sw + slot % sw;
         yt = back ? nty - 1 - slot / sw : slot / sw;

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(NT) void k_step2(KParams<T> P, char* state, size_t 
                                               int ntx, int nty, StampShare sh, bool back) {
     __shared__ Step2Lds<T, TW, TY, LOCAL> L;
     int xt, yt;
-    xcd_tile(blockIdx.x, ntx, nty, xt, yt, back);
+    xcd_tile(blockIdx.x, ntx, nty, xt, yt, back, SK != ST_THROUGH);
     step2_body<T, TW, TY, NT, STD, SK, false, LOCAL>(
         kernel_params<step2_reload<T>(TW, TY, NT)>(P),
         StateTile{state, off0, off1, off_stamp, sh, (int)blockIdx.x, xt, yt, 0}, L);
