@@ -170,6 +170,8 @@ inline Layout make_layout(int nx, int ny, size_t esz, size_t diag_blocks, int nh
 #define LBM_NT_MIN_BYTES (320ull << 20)
 #endif
 inline bool cached_state(const Layout& L) { return 2 * L.buf_bytes <= (size_t)LBM_NT_MIN_BYTES; }
+// The cache holds several such states at once: a third of it each.
+inline bool small_state(const Layout& L) { return 2 * L.buf_bytes <= (size_t(256) << 20) / 3; }
 // Streamed states are stored non-temporally only where a row is a whole number of
 // 128-byte lines: elsewhere a tile's row ends inside a line, which then goes to
 // memory in two parts; ordinary stores join them in the XCD's L2.  Measured on

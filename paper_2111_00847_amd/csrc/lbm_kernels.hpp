@@ -33,6 +33,9 @@ inline bool stamp_share_ok(int nx, int ny, int tw, int ty) {
 //        256 x 1024   64x16 6.7, 64x8 6.7, 32x16 6.9
 //        1024 x 512   32x16 12.8, 64x8 13.2, 64x16 13.5; 1024 x 1024 23.1, 23.7, 26.5
 //        4096 x 4096  64x8 364, 32x8 375, 32x16 395 (streamed from HBM)
+//        640 x 1089   32x16 18.2, 64x8 18.8 alone; three lattices at once, more than
+//                     the cache holds, 19.5 and 18.3: 32x16 only for states of which it
+//                     holds three (small_state)
 //   FP64 64 x 64      16x4 3.67, 32x4 4.3, 64x8 6.9; one-level 9.07
 //        200 x 100    32x4 4.3, 16x4 4.3, 32x8 5.6; one-level 14.5
 //        300 x 300    32x16 7.2, 32x8 7.35, 64x8 7.3
@@ -41,7 +44,7 @@ inline bool stamp_share_ok(int nx, int ny, int tw, int ty) {
 // CU; of one node per thread (576 threads) they serve single-round lattices.
 // S2_NONE: no tile shape has as many stamps as tiles (FP64, one row).
 enum Step2Shape { S2_NONE, S2_16x4, S2_32x4, S2_32x8_WIDE, S2_32x16, S2_64x16, S2_64x8, S2_32x8 };
-inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool cached) {
+inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool small) {
     auto tiles = [&](int tw, int ty) { return (long long)((nx + tw - 1) / tw) * ((ny + ty - 1) / ty); };
     auto one_round = [&](int tw, int ty) { return tiles(tw, ty) <= 256 && stamp_share_ok(nx, ny, tw, ty); };
     if (one_round(16, 4)) return S2_16x4;
@@ -50,7 +53,7 @@ inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool cached) {
     if (one_round(32, 16)) return S2_32x16;
     if (esz == 8) return stamp_share_ok(nx, ny, 32, 8) ? S2_32x8 : S2_NONE;
     if (one_round(64, 16)) return S2_64x16;
-    return cached && stamp_share_ok(nx, ny, 32, 16) ? S2_32x16 : S2_64x8;
+    return small && stamp_share_ok(nx, ny, 32, 16) ? S2_32x16 : S2_64x8;
 }
 
 // the Allen-Cahn step (either gradient scheme, not the corrected model) on a

@@ -634,7 +634,7 @@ static bool two_level_eligible(const Layout& L, int pf, int model) {
 }
 
 bool two_level_step(const Layout& L, int nx, int ny, int pf, int model) {
-    return two_level_eligible(L, pf, model) && step2_shape(nx, ny, L.esz, cached_state(L)) != S2_NONE;
+    return two_level_eligible(L, pf, model) && step2_shape(nx, ny, L.esz, small_state(L)) != S2_NONE;
 }
 
 bool two_level_path(const Layout& L, int nx, int ny, int pf, int model) {

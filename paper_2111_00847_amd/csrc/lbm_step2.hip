@@ -74,7 +74,7 @@ static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L
 // The launch's tiles (step2_shape).
 template <typename T>
 void launch_step2(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, bool back) {
-    switch (step2_shape(P.nx, P.ny, sizeof(T), cached_state(L))) {
+    switch (step2_shape(P.nx, P.ny, sizeof(T), small_state(L))) {
         case S2_16x4: launch_step2_shape<T, 16, 4, 256>(P, state, L, s, back); break;
         case S2_32x4: launch_step2_shape<T, 32, 4, 384>(P, state, L, s, back); break;
         case S2_32x8_WIDE: launch_step2_shape<T, 32, 8, 576>(P, state, L, s, back); break;

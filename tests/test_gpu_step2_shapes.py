@@ -21,7 +21,7 @@ torch = pytest.importorskip("torch")
 SHAPES = {   # size -> the shape the rule takes there (FP32 / FP64)
     (125, 60): "16x4", (64, 41): "32x4 (too few stamps for 16x4)", (250, 126): "32x4", (250, 250): "32x8, one round",
     (250, 500): "32x16, one round", (250, 1020): "64x16 / 32x8", (1020, 500): "32x16 cached / 32x8",
-    (2050, 1100): "64x8 streamed / 32x8", (17000, 1): "64x8 / one level",
+    (1020, 700): "64x8 cached / 32x8", (2050, 1100): "64x8 streamed / 32x8", (17000, 1): "64x8 / one level",
 }
 
 
