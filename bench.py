@@ -73,7 +73,7 @@ ALG_BYTES = {"f32": 168, "f64": 336}   # per lattice update: f, g read+write, (p
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "k_step2_rti_256x1024_traffic.json")
 # everything the headline's two-level kernel is compiled from (with the build flags)
 KERNEL_SOURCES = ["paper_2111_00847_amd/csrc/lbm_step2.hip", "paper_2111_00847_amd/csrc/lbm_step2.hpp",
-                  "paper_2111_00847_amd/csrc/lbm_fused.hpp",
+                  "paper_2111_00847_amd/csrc/lbm_fused.hpp", "paper_2111_00847_amd/csrc/lbm_addr.hpp",
                   "paper_2111_00847_amd/csrc/lbm_tile.hpp", "paper_2111_00847_amd/csrc/lbm_device.hpp",
                   "paper_2111_00847_amd/csrc/lbm_common.hpp", "paper_2111_00847_amd/build.py"]
 
