@@ -68,7 +68,9 @@ using BodyParams = typename std::conditional<RELOAD, ParamsPtr<T>, KParams<T>>::
 
 template <typename T>
 __device__ __forceinline__ KParams<T> params_at(ParamsPtr<T> p) {
+#ifdef __OPTIMIZE__   // unoptimised code keeps p in no scalar register, and reads anew anyway
     asm volatile("" : "+s"(p));
+#endif
     return *(const KParams<T>*)p;
 }
 template <typename T>
