@@ -820,7 +820,7 @@ template <typename T, int TW, int TY, int NT>
 static void tape_step2_launch(const KParams<T>& P, char* tape, size_t slot, int j, hipStream_t s) {
     const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
     const dim3 blk(TX, NT / TX);
-    auto go = [&](auto kernel) { kernel<<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty); };
+    auto go = [&](auto kernel) LBM_CALLS_STUB { kernel<<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty); };
     // slot j + 2 with ordinary stores while it and the next fit the last-level cache (the next launch reads it)
     const bool cached = 2 * slot <= (size_t)LBM_NT_MIN_BYTES;
     if (P.rates_std) cached ? go(k_tape_step2<T, TW, TY, NT, true, false>) : go(k_tape_step2<T, TW, TY, NT, true, true>);
@@ -870,7 +870,7 @@ static void launch_adj_step(const KParams<T>& P, const char* tape, size_t slot, 
                             size_t adj_bytes, hipStream_t s) {
     // 32-bit byte offsets while a tape slot and the adjoint buffer stay below 4 GiB
     const bool small = slot < (size_t(1) << 32) && adj_bytes < (size_t(1) << 32);
-    auto a_launch = [&](auto k32, auto k64, int nt) {
+    auto a_launch = [&](auto k32, auto k64, int nt) LBM_CALLS_STUB {
         if (small) k32<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
         else k64<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
     };

@@ -347,7 +347,7 @@ void launch_batch2(Step2Shape shape, int nitems, int ncases, const void* d_cases
                    hipStream_t s) {
     const BatchCase<T>* cases = reinterpret_cast<const BatchCase<T>*>(d_cases);
     const bool nts = total > (size_t)LBM_NT_MIN_BYTES;
-    auto go = [&](auto kernel, int nt) { kernel<<<nitems, dim3(TX, nt / TX), 0, s>>>(cases, ncases, nitems, state); };
+    auto go = [&](auto kernel, int nt) LBM_CALLS_STUB { kernel<<<nitems, dim3(TX, nt / TX), 0, s>>>(cases, ncases, nitems, state); };
     switch (shape) {   // the single-round shapes are far below the last-level cache
         case S2_16x4: go(k_step2_batch<T, 16, 4, 256, false, PER_ITEM>, 256); break;
         case S2_32x4: go(k_step2_batch<T, 32, 4, 384, false, PER_ITEM>, 384); break;

@@ -8,6 +8,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// On a host function that launches a kernel through a pointer: a kernel's host
+// stub has no type record for the sanitizer of indirect calls.
+#define LBM_CALLS_STUB __attribute__((no_sanitize("function")))
+
 namespace lbm {
 
 constexpr int Q = 9;

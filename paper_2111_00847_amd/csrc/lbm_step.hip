@@ -689,7 +689,7 @@ template <typename T>
 hipError_t launch_init(const KParams<T>& P, char* state, const Layout& L, const T* phi0, const T* u0,
                        const T* p0, int dtype, hipStream_t s) {
     const StateMeta meta = state_meta(state, L, dtype, stamp_of(0, 0));
-    auto go = [&](auto kernel) { kernel<<<grid1d(L.n), 256, 0, s>>>(P, phi0, u0, p0, state + L.off_buf[0], meta); };
+    auto go = [&](auto kernel) LBM_CALLS_STUB { kernel<<<grid1d(L.n), 256, 0, s>>>(P, phi0, u0, p0, state + L.off_buf[0], meta); };
     if (P.pf == 1) small_copy(L) ? go(k_init<T, true, uint32_t>) : go(k_init<T, true, uint64_t>);
     else small_copy(L) ? go(k_init<T, false, uint32_t>) : go(k_init<T, false, uint64_t>);
     return hipGetLastError();
@@ -714,7 +714,7 @@ hipError_t launch_import(const KParams<T>& P, char* state, const Layout& L, cons
                          const T* hist, int64_t step, int dtype, hipStream_t s) {
     const int cur = (int)(step & 1);
     const StateMeta meta = state_meta(state, L, dtype, stamp_of(step, cur));
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel) LBM_CALLS_STUB {
         kernel<<<grid1d(L.n), 256, 0, s>>>(P, f, g, step > 0 ? hist : nullptr, state + L.off_buf[cur], meta);
     };
     small_copy(L) ? go(k_import<T, uint32_t>) : go(k_import<T, uint64_t>);
@@ -724,7 +724,7 @@ hipError_t launch_import(const KParams<T>& P, char* state, const Layout& L, cons
 template <typename T>
 hipError_t launch_export(const KParams<T>& P, const char* state, const Layout& L, T* f, T* g, T* hist,
                          hipStream_t s) {
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel) LBM_CALLS_STUB {
         kernel<<<grid1d(L.n), 256, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, f, g, hist);
     };
     small_copy(L) ? go(k_export<T, uint32_t>) : go(k_export<T, uint64_t>);

@@ -56,7 +56,7 @@ static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L
     const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
     const StampShare sh = stamp_share((long long)L.nstamp, (long long)ntx * nty);
     const dim3 grd(ntx * nty), blk(TX, NT / TX);
-    auto go = [&](auto kernel) {
+    auto go = [&](auto kernel) LBM_CALLS_STUB {
         kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh, back);
     };
     // written through while the cache holds both copies, else the streamed store kind
