@@ -52,6 +52,22 @@ __device__ __forceinline__ void ghosts_h(const KParams<T>& P, bool need_prev, in
     }
 }
 
+// f(0), ..., f(N - 1) with the index a compile-time constant from the start.  The
+// positions of a thread (step2_body) are walked with it: in a loop over them, unrolled
+// later, their FP32 populations became one wide vector register, copied whole
+// between the loads of one position and the next, and each copy waits for the
+// loads before it -- the round trips of a tile one after the other.
+template <int N, typename F>
+__device__ __forceinline__ void each(F&& f) {
+    if constexpr (N > 0) {
+        each<N - 1>(f);
+        f(std::integral_constant<int, N - 1>());
+    }
+}
+
+// Waits until the wave's loads have arrived (vmcnt 0; the other counters are left).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 // LDS of one tile.  Arrays of A's region have the region's pitch, the phi windows
 // theirs.  LOCAL: the local gradient scheme hands B m^phiC of level n and needs
 // no window of the previous phi.
@@ -99,8 +115,7 @@ __host__ __device__ constexpr bool step2_reload(int tw, int ty, int nt) {
 // of the rest.  So the body keeps addresses off the vector unit (planes are
 // uniform buffer offsets, f and g of one direction share one byte offset, and
 // only tiles within four nodes of an edge of the lattice, `inner` false, look
-// at wraps and walls), and it reads the window's ring columns with the rows of
-// the region: the same cache lines.  Bounce-back costs B nothing: A's wall
+// at wraps and walls).  Bounce-back costs B nothing: A's wall
 // nodes store their reflected populations at the positions beyond the wall
 // that B pulls from.
 template <typename T, int TW, int TY, int NT, bool STD, StoreKind SK, bool MID = false, bool LOCAL = false, typename Tile>
@@ -121,74 +136,108 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
     const bool inner = x0 >= 4 && x0 + TW + 4 <= P.nx && y0 >= 4 && y0 + TY + 4 <= P.ny;
     const bool walls = P.wall_x || P.wall_y;
 
-    // position s of this thread in A's window; whether it lies in A's region
-    auto window_pos = [&](int s, int& wx, int& wy) -> bool {
-        const int idx = tid + s * NT;
-        wy = idx / WW;
-        wx = idx - wy * WW;
-        return (s + 1) * NT <= NW || idx < NW;
+    // position s of this thread in A's window, row by row.  Of two positions to a
+    // thread, the rows of the region first and the ring's two rows last: fewer waves
+    // have two positions to step in A (64 x 8 tiles: 5 of 8 against 8; us per level,
+    // FP32, 4096 x 4096 344 / 352, 2048 x 1200 57.1 / 58.4, 1024 x 1024 22.5 / 22.8; with
+    // one or three positions plain order is 0-2% faster).  The ring's columns come
+    // with the rows, from the same cache lines.
+    // Returns its index in the window; beyond NW: none.
+    auto window_pos = [&](int s, int& wx, int& wy) -> int {
+        const int idx = tid + s * NT, row = idx / WW;
+        wx = idx - row * WW;
+        wy = S != 2 ? row : (row < AH ? row + 1 : (row == AH ? 0 : WH - 1));
+        return S != 2 || idx >= NW ? idx : wy * WW + wx;
     };
+    // whether it lies in A's region
     auto in_region = [](int wx, int wy) -> bool {
         return (unsigned)(wx - 1) < (unsigned)AW && (unsigned)(wy - 1) < (unsigned)AH;
     };
 
     // ---- A: loads of the window (f, history phi) and of the region (g, history)
     T f[S][9], g[S][9], hp[S], hu[S], hv[S], hmx[S], hmy[S], f0s[S];
-    bool ok[S];
+    bool ok[S], reg[S];
     int nxi[S], nyi[S];
-    auto load = [&](CopyAddr<uint32_t> sb) {
+    uint32_t off[S][9];
+    const CopyAddr<uint32_t> sb = tile.source(bytes);
+    auto load_f = [&](auto index) {
+        constexpr int s = decltype(index)::value;
+        int wx, wy;
+        const int at = window_pos(s, wx, wy);
+        ok[s] = ((s + 1) * NT <= NW || at < NW) && neighbour_offsets<T, uint32_t, -1>(P, inner, x0 - 3 + wx, y0 - 3 + wy, off[s], nxi[s], nyi[s]);
+        reg[s] = ok[s] && in_region(wx, wy);
+        if (ok[s]) {
+            f0s[s] = sb.template ld<T>(off[s][0], 0);
+            hp[s] = sb.template ld<T>(off[s][0], 18 * plB);
 #pragma unroll
-        for (int s = 0; s < S; s++) {
-            int wx, wy;
-            const bool in = window_pos(s, wx, wy);
-            uint32_t off[9];
-            ok[s] = in && neighbour_offsets<T, uint32_t, -1>(P, inner, x0 - 3 + wx, y0 - 3 + wy, off, nxi[s], nyi[s]);
-            if (ok[s]) {
-                f0s[s] = sb.template ld<T>(off[0], 0);
-                hp[s] = sb.template ld<T>(off[0], 18 * plB);
+            for (int i = 1; i < Q; i++) f[s][i] = sb.template ld<T>(off[s][i], pair_plane(i) * plB);
+        }
+    };
+    auto load_g = [&](auto index) {
+        constexpr int s = decltype(index)::value;
+        if (reg[s]) {
+            g[s][0] = sb.template ld<T>(off[s][0], 9 * plB);
 #pragma unroll
-                for (int i = 1; i < Q; i++) f[s][i] = sb.template ld<T>(off[i], pair_plane(i) * plB);
-                if (in_region(wx, wy)) {
-                    g[s][0] = sb.template ld<T>(off[0], 9 * plB);
-#pragma unroll
-                    for (int i = 1; i < Q; i++) g[s][i] = sb.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
-                    hu[s] = sb.template ld<T>(off[0], 19 * plB);
-                    hv[s] = sb.template ld<T>(off[0], 20 * plB);
-                    if constexpr (LOCAL) {
-                        hmx[s] = sb.template ld<T>(off[0], 21 * plB);
-                        hmy[s] = sb.template ld<T>(off[0], 22 * plB);
-                    }
-                }
+            for (int i = 1; i < Q; i++) g[s][i] = sb.template ld<T>(off[s][i], (9 + pair_plane(i)) * plB);
+            hu[s] = sb.template ld<T>(off[s][0], 19 * plB);
+            hv[s] = sb.template ld<T>(off[s][0], 20 * plB);
+            if constexpr (LOCAL) {
+                hmx[s] = sb.template ld<T>(off[s][0], 21 * plB);
+                hmy[s] = sb.template ld<T>(off[s][0], 22 * plB);
             }
         }
     };
-    const int64_t lev = tile.load(load, bytes);
+    // The memory system sets the pace of this phase.  On streamed FP32 states a
+    // position's g follows its f, each once the loads before it are in: all loads of
+    // a tile at once leave less time in which one tile's loads run under another's
+    // arithmetic.  Elsewhere all f, then all g; three positions to a thread (the FP32
+    // batch's 32 x 8 tiles) by position, and those and FP64 rows of broken lines without
+    // the wait.  Measured on MI355X, us per level, no wait / by position / f then g:
+    // FP32 4096 x 4096 362 / 346 / 368, 3072 x 2000 137 / 132 / 139, 2048 x 1200 59.6 /
+    // 57.5 / 60.1, cached 1280 x 1024 27.7 / 27.4 / 27.1, a batch of 64 cases 95.5 / 94.2 /
+    // 94.5, by position without the wait 93.3; FP64 1999 x 2203 195 / 199 / 196, 3072 x 2000
+    // 274 / 273 / 270, cached 1000 x 700 33.1 / 32.9 / 31.4, 200 x 100 5.3 / 5.05 / 5.0.
+    constexpr bool f32 = sizeof(T) == 4, waits = f32 ? S <= 2 : SK != ST_PLAIN;
+    if constexpr (f32 && (SK != ST_THROUGH || S > 2)) {
+        each<S>([&](auto index) {
+            load_f(index);
+            if (waits) wait_loads();
+            load_g(index);
+        });
+    } else {
+        each<S>(load_f);
+        if (waits) wait_loads();
+        each<S>(load_g);
+    }
+    const int64_t lev = tile.level();
     const bool first = lev == 0;
     T* const pa = &L.pa[0][0];
     T* const pp = &L.pp[0][0];
     double phid[S];
-#pragma unroll
-    for (int s = 0; s < S; s++) {
+    each<S>([&](auto index) {
+        constexpr int s = decltype(index)::value;
         if (ok[s]) {
             const double f0 = rest_decode(f0s[s], hp[s], P.rest_w);
             f[s][0] = (T)f0;
             phid[s] = f0 + moving_sum_d(f[s]);
-            pa[tid + s * NT] = (T)phid[s];
-            if constexpr (!LOCAL) pp[tid + s * NT] = hp[s];
+            int wx, wy;
+            const int at = window_pos(s, wx, wy);
+            pa[at] = (T)phid[s];
+            if constexpr (!LOCAL) pp[at] = hp[s];
         }
-    }
+    });
     __syncthreads();
     if (!inner) ghosts_h<T, WW, WH, 3, NT, WW>(params_at<T>(params), !first && !LOCAL, x0, y0, L.pa, L.pp, tid);
 
     // ---- A: the step of level n on the region
-#pragma unroll
-    for (int s = 0; s < S; s++) {
+    each<S>([&](auto index) {
+        constexpr int s = decltype(index)::value;
         int wx, wy;
-        window_pos(s, wx, wy);
-        if (!ok[s] || !in_region(wx, wy)) continue;
+        const int at = window_pos(s, wx, wy);
+        if (!reg[s]) return;
         const KParams<T>& P = params_at<T>(params);
         const int ax = wx - 1, ay = wy - 1;
-        const int idx = tid + s * NT - (WW - AW) * wy - (AW + 1);   // ay * AW + ax
+        const int idx = at - (WW - AW) * wy - (AW + 1);   // ay * AW + ax
         T gx, gy, lap, gxp = T(0), gyp = T(0), lp, php = T(0), up = T(0), vp = T(0);
         win_stencil_at(L.pa, wx, wy, gx, gy, lap);
         const Macro<T> M = [&]() -> Macro<T> {
@@ -256,7 +305,7 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
                 }
             }
         }
-    }
+    });
     __syncthreads();
 
     // ---- B: phi of level n + 1 on the tile and its one-node ring, from A's f
@@ -365,12 +414,11 @@ struct StateTile {
     __device__ int64_t* stamp() const {
         return reinterpret_cast<int64_t*>(state + off_stamp) + (size_t)t * sh.sq + (t < sh.srem ? t : sh.srem);
     }
-    template <typename Load>
-    __device__ int64_t load(Load&& loads, uint32_t bytes) {
+    __device__ CopyAddr<uint32_t> source(uint32_t bytes) {
         sv = stamp()[0];
-        loads(CopyAddr<uint32_t>(state + (stamp_copy(sv) ? off1 : off0), bytes));
-        return stamp_level(sv);
+        return CopyAddr<uint32_t>(state + (stamp_copy(sv) ? off1 : off0), bytes);
     }
+    __device__ int64_t level() const { return stamp_level(sv); }
     __device__ char* dst() const { return state + (stamp_copy(sv) ? off0 : off1); }
     __device__ void done(int tid) const {
         if (tid < sh.sq + (t < sh.srem ? 1 : 0)) stamp()[tid] = stamp_of(stamp_level(sv) + 2, 1 - stamp_copy(sv));
@@ -385,11 +433,8 @@ struct TapeTile {
     char* d;
     int64_t lev;
     int xt, yt;
-    template <typename Load>
-    __device__ int64_t load(Load&& loads, uint32_t bytes) const {
-        loads(CopyAddr<uint32_t>(src, bytes));
-        return lev;
-    }
+    __device__ CopyAddr<uint32_t> source(uint32_t bytes) const { return CopyAddr<uint32_t>(src, bytes); }
+    __device__ int64_t level() const { return lev; }
     __device__ char* dst() const { return d; }
     __device__ void done(int) const {}
 };
