@@ -82,7 +82,9 @@ struct Step2Lds {
     T ga[Q][NA];                         // post-collision g of A (tile and one-node ring)
     T pb[GH][GW + 1];                    // phi of level n + 1 (with wall ghosts)
     T ua[NA], va[NA];                    // velocity of level n on the tile (B's history)
-    T mxa[LOCAL ? NA : 1], mya[LOCAL ? NA : 1];
+    // LOCAL: m^phiC of level n on the tile (on the tile alone, so that two workgroups of
+    // FP64 32 x 8 tiles fit a CU: 80.6 KB)
+    T mxa[LOCAL ? TW * TY : 1], mya[LOCAL ? TW * TY : 1];
 };
 
 // Whether the body reads its parameters anew in each phase (params_at): in FP64,
@@ -276,10 +278,11 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
             // B's history of the velocity (read on the tile only)
             L.ua[idx] = M.u;
             L.va[idx] = M.v;
-            if constexpr (LOCAL) {
-                L.mxa[idx] = M.mx;
-                L.mya[idx] = M.my;
-            }
+            if constexpr (LOCAL)
+                if ((unsigned)(ax - 2) < (unsigned)TW && (unsigned)(ay - 2) < (unsigned)TY) {
+                    L.mxa[(ay - 2) * TW + ax - 2] = M.mx;
+                    L.mya[(ay - 2) * TW + ax - 2] = M.my;
+                }
             if (!inner && walls) {   // what B's pulls from beyond a wall find there
 #pragma unroll
                 for (int i = 1; i < Q; i++)
@@ -360,7 +363,7 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
                 const T up = L.ua[c], vp = L.va[c];
                 local_grad(P, fb, gb, phi, lap, php * up, php * vp, gx, gy);
                 return macro<T, false, true>(P, gb, phi, gx, gy, lap, false, php, T(0), T(0), up, vp, T(0), T(0),
-                                             L.mxa[c], L.mya[c]);
+                                             L.mxa[ly * TW + lx], L.mya[ly * TW + lx]);
             } else {
                 win_stencil_at(L.pa, lx + 3, ly + 3, gxp, gyp, lp);
                 return macro(P, gb, L.pb[ly + 1][lx + 1], gx, gy, lap, false, L.pa[ly + 3][lx + 3], gxp, gyp,
