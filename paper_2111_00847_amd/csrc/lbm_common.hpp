@@ -163,7 +163,7 @@ inline Layout make_layout(int nx, int ny, size_t esz, size_t diag_blocks, int nh
     return L;
 }
 
-// The step kernels store the state with ordinary stores while both copies fit
+// The one-level step kernels store the state with ordinary stores while both copies fit
 // in this many bytes, so that the state (or most of it) stays in the 256 MB
 // last-level cache from one step to the next, and non-temporally above.
 // Measured on MI355X, FP32 (state of both copies): 256 x 1024 (46 MB) +2%,
@@ -173,17 +173,20 @@ inline Layout make_layout(int nx, int ny, size_t esz, size_t diag_blocks, int nh
 #ifndef LBM_NT_MIN_BYTES
 #define LBM_NT_MIN_BYTES (320ull << 20)
 #endif
-inline bool cached_state(const Layout& L) { return 2 * L.buf_bytes <= (size_t)LBM_NT_MIN_BYTES; }
+inline bool cached_bytes(size_t bytes) { return bytes <= (size_t)LBM_NT_MIN_BYTES; }
+inline bool cached_state(const Layout& L) { return cached_bytes(2 * L.buf_bytes); }
 // The cache holds several such states at once: a third of it each.
-inline bool small_state(const Layout& L) { return 2 * L.buf_bytes <= (size_t(256) << 20) / 3; }
-// Streamed states are stored non-temporally only where a row is a whole number of
+inline bool small_bytes(size_t bytes) { return bytes <= (size_t(256) << 20) / 3; }
+inline bool small_state(const Layout& L) { return small_bytes(2 * L.buf_bytes); }
+// A lone streamed state (below 4 GiB a copy) is stored non-temporally only where a row is a whole number of
 // 128-byte lines: elsewhere a tile's row ends inside a line, which then goes to
 // memory in two parts; ordinary stores join them in the XCD's L2.  Measured on
 // MI355X, us per level, ordinary against non-temporal: rows of broken lines FP32
 // 5000 x 4500 518 / 553, 3000 x 3000 202 / 211, FP64 1999 x 2203 194 / 227,
 // Cahn-Hilliard FP32 1601 x 1601 105 / 129, 3000 x 3000 356 / 393; of whole lines
 // FP32 4096 x 4096 365 / 358, 2688 x 2216 137 / 134, 4000 x 4100 373 / 363.
-inline bool whole_lines(const Layout& L, int nx) { return (size_t)nx * L.esz % 128 == 0; }
+inline bool whole_rows(int nx, size_t esz) { return (size_t)nx * esz % 128 == 0; }
+inline bool whole_lines(const Layout& L, int nx) { return whole_rows(nx, L.esz); }
 inline bool plain_stores(const Layout& L, int nx) { return cached_state(L) || !whole_lines(L, nx); }
 // Both copies within the 256 MB last-level cache itself (the plain step then
 // loads g after its window barrier).

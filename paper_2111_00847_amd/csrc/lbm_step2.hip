@@ -21,8 +21,8 @@
 // recomputation (the region of A is (TW + 4)(TY + 4) nodes) and L2 reads of
 // the neighbouring tiles' rows, not HBM traffic beyond those rows: a launch
 // reads the state once and writes it once for two levels.  On states larger than
-// the last-level cache the sweeps alternate in direction (xcd_tile) and rows of
-// whole cache lines are stored non-temporally (whole_lines).
+// the last-level cache the sweeps alternate in direction (xcd_tile); step2_store says
+// how the copy is stored.
 //
 // Where the time of a launch goes (wave clocks, 256 x 1024 FP32, 64 x 16 tiles, one
 // per CU, before the window's ring was read with the region and the stores wrote
@@ -36,16 +36,20 @@
 
 namespace lbm {
 
-// Two levels of one tile per workgroup, tiles dealt to the XCDs (xcd_tile).
+enum { BACK = 1, STRIPS = 2 };
+
+// Two levels of one tile per workgroup, tiles dealt to the XCDs (xcd_tile) in
+// `order`: sweep direction, and strips for streamed states.  What is written through is
+// cached and swept forward in bands, and does not read it.
 // P is the kernel's first argument: the body reads it from the argument
 // segment.  LOCAL: the local gradient scheme (Eq. local; the general collision,
 // as the one-level kernel runs it).
 template <typename T, int TW, int TY, int NT, bool STD, StoreKind SK, bool LOCAL>
 __global__ __launch_bounds__(NT) void k_step2(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stamp,
-                                              int ntx, int nty, StampShare sh, bool back) {
+                                              int ntx, int nty, StampShare sh, int order) {
     __shared__ Step2Lds<T, TW, TY, LOCAL> L;
     int xt, yt;
-    xcd_tile(blockIdx.x, ntx, nty, xt, yt, back, SK != ST_THROUGH);
+    xcd_tile(blockIdx.x, ntx, nty, xt, yt, SK != ST_THROUGH && (order & BACK), SK != ST_THROUGH && (order & STRIPS));
     step2_body<T, TW, TY, NT, STD, SK, false, LOCAL>(
         kernel_params<step2_reload<T>(TW, TY, NT)>(P),
         StateTile{state, off0, off1, off_stamp, sh, (int)blockIdx.x, xt, yt, 0}, L);
@@ -56,19 +60,21 @@ static void launch_step2_shape(const KParams<T>& P, char* state, const Layout& L
     const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
     const StampShare sh = stamp_share((long long)L.nstamp, (long long)ntx * nty);
     const dim3 grd(ntx * nty), blk(TX, NT / TX);
+    const int order = (back ? BACK : 0) | (cached_state(L) ? 0 : STRIPS);
     auto go = [&](auto kernel) LBM_CALLS_STUB {
-        kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh, back);
+        kernel<<<grd, blk, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, sh, order);
     };
-    // written through while the cache holds both copies, else the streamed store kind
     auto by_store = [&](auto kind) {
         constexpr StoreKind SK = decltype(kind)::value;
         if (P.grad == 1) go(k_step2<T, TW, TY, NT, false, SK, true>);
         else if (P.rates_std) go(k_step2<T, TW, TY, NT, true, SK, false>);
         else go(k_step2<T, TW, TY, NT, false, SK, false>);
     };
-    if (cached_state(L)) by_store(std::integral_constant<StoreKind, ST_THROUGH>());
-    else if (whole_lines(L, P.nx)) by_store(std::integral_constant<StoreKind, ST_NT>());
-    else by_store(std::integral_constant<StoreKind, ST_PLAIN>());
+    switch (step2_store(2 * L.buf_bytes, whole_lines(L, P.nx))) {
+        case ST_THROUGH: by_store(std::integral_constant<StoreKind, ST_THROUGH>()); break;
+        case ST_NT: by_store(std::integral_constant<StoreKind, ST_NT>()); break;
+        default: by_store(std::integral_constant<StoreKind, ST_PLAIN>());
+    }
 }
 
 // The launch's tiles (step2_shape).
