@@ -107,7 +107,7 @@ void k_step_batch(const BatchCase<T>* __restrict__ cases, int ncases, int nitems
 // holds one entry per item (its case's), so that the workgroup reads its case
 // directly instead of counting item_begin over the cases first (one round
 // trip and a barrier fewer before the tile's loads).
-template <typename T, int TW, int TY, int NT, bool NTS, bool PER_ITEM>
+template <typename T, int TW, int TY, int NT, StoreKind SK, bool PER_ITEM>
 __global__ __launch_bounds__(NT) void k_step2_batch(const BatchCase<T>* __restrict__ cases, int ncases, int nitems,
                                                     char* batch_state) {
     __shared__ Step2Lds<T, TW, TY> L;
@@ -117,8 +117,8 @@ __global__ __launch_bounds__(NT) void k_step2_batch(const BatchCase<T>* __restri
     const StateTile tile{batch_state + C.base, C.off0, C.off1, C.off_stamp, C.share, local, local % C.ntx,
                          local / C.ntx, 0};
     auto body = [&](auto params) {
-        if (C.P.rates_std) step2_body<T, TW, TY, NT, true, NTS ? ST_NT : ST_THROUGH>(params, tile, L);
-        else step2_body<T, TW, TY, NT, false, NTS ? ST_NT : ST_THROUGH>(params, tile, L);
+        if (C.P.rates_std) step2_body<T, TW, TY, NT, true, SK>(params, tile, L);
+        else step2_body<T, TW, TY, NT, false, SK>(params, tile, L);
     };
     body(memory_params<step2_reload<T>(TW, TY, NT)>(C.P));
 }
@@ -202,6 +202,7 @@ struct lbm_batch {
     // lbm_batch_levels_per_launch reports (the size rule)
     bool two_level = false;
     lbm::Step2Shape shape2 = lbm::S2_NONE;
+    bool whole = false;   // whole_batch
     void* d_cases2 = nullptr;
     int nitems2 = 0;
     // graph of `graph_steps` levels for (graph_state, graph_stream)
@@ -342,25 +343,31 @@ void launch_batch_once(lbm_batch* B, char* state, hipStream_t s) {
 
 // One two-level launch over `nitems` items of a table for tiles of `shape`
 // (PER_ITEM: one entry per item, as upload_cases2 writes it; else one per case).
+// whole: whole_batch (step2_store; us per level, FP32,
+// non-temporal or through against ordinary stores: 60 cases of 250 x 250 134 / 98, 28 of
+// them 57 / 48, 10 of 500 x 300 38.7 / 32.5; FP64 13 of 250 x 250 50.2 / 47.3, 30 107.2 /
+// 107.9).
 template <typename T, bool PER_ITEM>
-void launch_batch2(Step2Shape shape, int nitems, int ncases, const void* d_cases, size_t total, char* state,
-                   hipStream_t s) {
+void launch_batch2(Step2Shape shape, int nitems, int ncases, const void* d_cases, size_t total, bool whole,
+                   char* state, hipStream_t s) {
     const BatchCase<T>* cases = reinterpret_cast<const BatchCase<T>*>(d_cases);
-    const bool nts = total > (size_t)LBM_NT_MIN_BYTES;
     auto go = [&](auto kernel, int nt) LBM_CALLS_STUB { kernel<<<nitems, dim3(TX, nt / TX), 0, s>>>(cases, ncases, nitems, state); };
+    const StoreKind kind = step2_store(total, whole);
     switch (shape) {   // the single-round shapes are far below the last-level cache
-        case S2_16x4: go(k_step2_batch<T, 16, 4, 256, false, PER_ITEM>, 256); break;
-        case S2_32x4: go(k_step2_batch<T, 32, 4, 384, false, PER_ITEM>, 384); break;
-        case S2_32x8_WIDE: go(k_step2_batch<T, 32, 8, 576, false, PER_ITEM>, 576); break;
-        case S2_32x16: go(k_step2_batch<T, 32, 16, 512, false, PER_ITEM>, 512); break;
+        case S2_16x4: go(k_step2_batch<T, 16, 4, 256, ST_THROUGH, PER_ITEM>, 256); break;
+        case S2_32x4: go(k_step2_batch<T, 32, 4, 384, ST_THROUGH, PER_ITEM>, 384); break;
+        case S2_32x8_WIDE: go(k_step2_batch<T, 32, 8, 576, ST_THROUGH, PER_ITEM>, 576); break;
+        case S2_32x16: go(k_step2_batch<T, 32, 16, 512, ST_THROUGH, PER_ITEM>, 512); break;
         case S2_32x8:
-            if (nts) go(k_step2_batch<T, 32, 8, 256, true, PER_ITEM>, 256);
-            else go(k_step2_batch<T, 32, 8, 256, false, PER_ITEM>, 256);
+            if (kind == ST_NT) go(k_step2_batch<T, 32, 8, 256, ST_NT, PER_ITEM>, 256);
+            else if (kind == ST_PLAIN) go(k_step2_batch<T, 32, 8, 256, ST_PLAIN, PER_ITEM>, 256);
+            else go(k_step2_batch<T, 32, 8, 256, ST_THROUGH, PER_ITEM>, 256);
             break;
         default:
             if constexpr (sizeof(T) == 4) {
-                if (nts) go(k_step2_batch<T, 64, 8, 512, true, PER_ITEM>, 512);
-                else go(k_step2_batch<T, 64, 8, 512, false, PER_ITEM>, 512);
+                if (kind == ST_NT) go(k_step2_batch<T, 64, 8, 512, ST_NT, PER_ITEM>, 512);
+                else if (kind == ST_PLAIN) go(k_step2_batch<T, 64, 8, 512, ST_PLAIN, PER_ITEM>, 512);
+                else go(k_step2_batch<T, 64, 8, 512, ST_THROUGH, PER_ITEM>, 512);
             }
     }
 }
@@ -370,7 +377,7 @@ template <typename T>
 void launch_batch_levels(lbm_batch* B, char* state, int64_t n, hipStream_t s) {
     if (B->shape2 != S2_NONE) {
         for (int64_t t = 0; t + 2 <= n; t += 2)
-            launch_batch2<T, true>(B->shape2, B->nitems2, B->ncases, B->d_cases2, B->total, state, s);
+            launch_batch2<T, true>(B->shape2, B->nitems2, B->ncases, B->d_cases2, B->total, B->whole, state, s);
         if (n & 1) launch_batch_once<T>(B, state, s);
     } else {
         for (int64_t t = 0; t < n; t++) launch_batch_once<T>(B, state, s);
@@ -537,6 +544,17 @@ bool two_level_batch(const lbm_params* cases, int ncases) {
     return (e && e[0] == '1' && e[1] == 0) || tiles8 >= 256;
 }
 
+// Whether a batch counts as one of whole cache lines in step2_store: most of its nodes do.
+bool whole_batch(const lbm_params* cases, int ncases) {
+    long long broken = 0, n = 0;
+    for (int c = 0; c < ncases; c++) {
+        const long long nodes = (long long)cases[c].nx * cases[c].ny;
+        n += nodes;
+        if (!whole_rows(cases[c].nx, cases[c].dtype == LBM_F64 ? 8 : 4)) broken += nodes;
+    }
+    return 2 * broken <= n;
+}
+
 // Tile shape of the two-level launch: the smallest that gives no CU two tiles, as
 // for a single lattice (step2_shape), else 32 x 8 tiles, two (FP64) to four (FP32)
 // workgroups of 256 threads to a CU; S2_NONE: one level per launch.  Measured on
@@ -643,7 +661,7 @@ int batch_step_noalloc_t(const lbm_params* cases, int ncases, char* state, int64
         int tw, ty;
         step2_tile_size(shape, &tw, &ty);
         const int nitems = put_cases(tw, ty);
-        for (; t + 2 <= nsteps; t += 2) launch_batch2<T, false>(shape, nitems, ncases, table, total, state, s);
+        for (; t + 2 <= nsteps; t += 2) launch_batch2<T, false>(shape, nitems, ncases, table, total, whole_batch(cases, ncases), state, s);
     }
     if (t < nsteps) {
         // the untuned plan's shape: 8-row tiles, 64 x 4 threads (64 x 8 for the wide bodies), one
@@ -701,6 +719,7 @@ int lbm_batch_create(const lbm_params* cases, int32_t ncases, int32_t autotune, 
     hipError_t e = B->dtype == LBM_F32 ? upload_cases<float>(B, B->ty) : upload_cases<double>(B, B->ty);
     B->two_level = two_level_batch(cases, ncases);
     B->shape2 = batch_shape2(cases, ncases);
+    B->whole = whole_batch(cases, ncases);
     if (e == hipSuccess && B->shape2 != S2_NONE) e = B->dtype == LBM_F32 ? upload_cases2<float>(B) : upload_cases2<double>(B);
     if (e != hipSuccess) {
         lbm_batch_destroy(B);
