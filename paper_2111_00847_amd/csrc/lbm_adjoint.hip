@@ -228,14 +228,14 @@ void k_tape_step(KParams<T> P, char* tape, size_t slot, int j, int ntx, int nty)
 // intermediate level, stored non-temporally: the adjoint reads it back later)
 // and slot j + 2, on the lattices where lbm_step takes two levels per launch;
 // bitwise the levels of two k_tape_step launches.
-template <typename T, int TW, int TY, int NT, bool STD, bool NTS>
+template <typename T, int TW, int TY, int NT, bool STD, StoreKind SK>
 __global__ __launch_bounds__(NT) void k_tape_step2(KParams<T> P, char* tape, size_t slot, int j, int ntx, int nty) {
     __shared__ Step2Lds<T, TW, TY> L;
     const int64_t n = reinterpret_cast<const TapeHeader*>(tape)->n0 + j;
     char* src = tape + TAPE_HDR + (size_t)j * slot;
     int xt, yt;
     xcd_tile(blockIdx.x, ntx, nty, xt, yt);
-    step2_body<T, TW, TY, NT, STD, NTS ? ST_NT : ST_THROUGH, true>(kernel_params<step2_reload<T>(TW, TY, NT)>(P),
+    step2_body<T, TW, TY, NT, STD, SK, true>(kernel_params<step2_reload<T>(TW, TY, NT)>(P),
                                               TapeTile{src, src + slot, src + 2 * slot, n, xt, yt}, L);
 }
 
@@ -821,10 +821,19 @@ static void tape_step2_launch(const KParams<T>& P, char* tape, size_t slot, int 
     const int ntx = (P.nx + TW - 1) / TW, nty = (P.ny + TY - 1) / TY;
     const dim3 blk(TX, NT / TX);
     auto go = [&](auto kernel) LBM_CALLS_STUB { kernel<<<ntx * nty, blk, 0, s>>>(P, tape, slot, j, ntx, nty); };
-    // slot j + 2 with ordinary stores while it and the next fit the last-level cache (the next launch reads it)
-    const bool cached = 2 * slot <= (size_t)LBM_NT_MIN_BYTES;
-    if (P.rates_std) cached ? go(k_tape_step2<T, TW, TY, NT, true, false>) : go(k_tape_step2<T, TW, TY, NT, true, true>);
-    else cached ? go(k_tape_step2<T, TW, TY, NT, false, false>) : go(k_tape_step2<T, TW, TY, NT, false, true>);
+    auto by_store = [&](auto kind) {
+        constexpr StoreKind SK = decltype(kind)::value;
+        P.rates_std ? go(k_tape_step2<T, TW, TY, NT, true, SK>) : go(k_tape_step2<T, TW, TY, NT, false, SK>);
+    };
+    // Slot j + 2 is read by the next launch: written through while it and the next fit the
+    // last-level cache, else non-temporally, as slot j + 1 is.  Rows that end inside a
+    // cache line: both slots with ordinary stores whatever the size, since a tape as a
+    // whole always leaves the cache (step2_store; us per level, FP32, against the
+    // others: 1030 x 512 20.8 / 28.7, 1000 x 300 14.0 / 15.5, 1000 x 1000 39.9 / 44.0, 1500 x
+    // 1000 60.7 / 78.2, 1999 x 1100 82.8 / 124).
+    if (!whole_rows(P.nx, sizeof(T))) by_store(std::integral_constant<StoreKind, ST_PLAIN>());
+    else if (cached_bytes(2 * slot)) by_store(std::integral_constant<StoreKind, ST_THROUGH>());
+    else by_store(std::integral_constant<StoreKind, ST_NT>());
 }
 
 // The tiles of the two-level launch of lbm_step (step2_shape).

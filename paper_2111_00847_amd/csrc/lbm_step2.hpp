@@ -102,11 +102,11 @@ __host__ __device__ constexpr bool step2_reload(int tw, int ty, int nt) {
 // threads (64 x NT/64).  `tile` (StateTile, TapeTile) says which tile, where its
 // level is read and where level + 2 goes.  MID also stores the tile's
 // intermediate level (what a one-level step would write) into the copy at
-// tile.mid, non-temporally.  Every thread owns up to S positions of A's window
-// and one node of the tile in B.  NTS: non-temporal stores into the destination
-// copy; otherwise they write through the XCD's L2 (device scope), so that no
-// dirty lines are left to flush between two launches (256 x 1024 FP32: 14.7 to
-// 13.4 us per launch; 1024 x 512: 29.2 to 27.2).
+// tile.mid, non-temporally (with ordinary stores where SK is).  Every thread owns
+// up to S positions of A's window and one node of the tile in B.  SK: how the
+// destination copy is stored; written through the XCD's L2 it leaves no dirty
+// lines to flush between two launches (256 x 1024 FP32: 14.7 to 13.4 us per
+// launch; 1024 x 512: 29.2 to 27.2).
 // LOCAL: the Allen-Cahn step with the local gradient scheme (Eq. local; the
 // one-level body of lbm_local_step.hpp): grad phi of levels >= 1 from each
 // node's own f and g, a history of five planes (phi, u, v and m^phiC of the
@@ -297,14 +297,15 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
                 if (ax >= 2 && ax < AW - 2 && ay >= 2 && ay < AH - 2 && x < P.nx && y < P.ny) {
                     const CopyAddr<uint32_t> mb(tile.mid, bytes);
                     const uint32_t k = ((uint32_t)y * (uint32_t)P.nx + (uint32_t)x) * ES;
-                    mb.template st<ST_NT>(k, 0, f0e);
+                    constexpr StoreKind MK = SK == ST_PLAIN ? ST_PLAIN : ST_NT;
+                    mb.template st<MK>(k, 0, f0e);
 #pragma unroll
-                    for (int i = 1; i < Q; i++) mb.template st<ST_NT>(k, i * plB, f[s][i]);
+                    for (int i = 1; i < Q; i++) mb.template st<MK>(k, i * plB, f[s][i]);
 #pragma unroll
-                    for (int i = 0; i < Q; i++) mb.template st<ST_NT>(k, (9 + i) * plB, g[s][i]);
-                    mb.template st<ST_NT>(k, 18 * plB, M.phi);
-                    mb.template st<ST_NT>(k, 19 * plB, M.u);
-                    mb.template st<ST_NT>(k, 20 * plB, M.v);
+                    for (int i = 0; i < Q; i++) mb.template st<MK>(k, (9 + i) * plB, g[s][i]);
+                    mb.template st<MK>(k, 18 * plB, M.phi);
+                    mb.template st<MK>(k, 19 * plB, M.u);
+                    mb.template st<MK>(k, 20 * plB, M.v);
                 }
             }
         }

@@ -51,3 +51,40 @@ def test_batch_equals_lone_one_level_runs(kind, dtype):
                     assert torch.equal(got[q], want[q]), (k, q)
     finally:
         os.environ.pop("LBM_TWO_LEVEL", None)
+
+
+TAPES = {   # size -> the tile shape the rule takes there (FP32 / FP64)
+    (125, 60): "16x4", (250, 126): "32x4", (250, 250): "32x8, one round", (256, 250): "32x8, one round, whole rows",
+    (250, 500): "32x16, one round", (250, 1020): "64x16 / 32x8", (256, 1020): "64x16 / 32x8, whole rows",
+    (1020, 500): "32x16 / 32x8", (1024, 500): "32x16 / 32x8, whole rows", (1020, 700): "64x8 / 32x8",
+    (2050, 1100): "64x8 / 32x8, streamed", (2048, 1100): "64x8 / 32x8, streamed, whole rows",
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("size", list(TAPES), ids=[f"{a}x{b}" for a, b in TAPES])
+def test_tape_slots_equal_one_level_launches(size, dtype):
+    """Every slot of a tape -- those between two launches, those a launch stores
+    on its way, and the last one of an odd count -- holds the level that
+    one-level launches give."""
+    from paper_2111_00847_amd import api
+    from paper_2111_00847_amd.sim import Sim
+    nx, ny = size
+    case = _case(nx, ny, dtype)
+    phi0, u0, p0 = W.random_state_fields(case, seed=nx + ny)
+    print(f"tape {nx}x{ny} {dtype}: {TAPES[size]}", flush=True)
+    a, b, c = (Sim(case).init(phi0, u0, p0) for _ in range(3))
+    slots = 6
+    tape = api.new_tape(a.p, slots)
+    api.lbm_tape_record(a.p, a.state, tape, slots)
+    os.environ["LBM_TWO_LEVEL"] = "0"
+    try:
+        for j in range(slots):
+            api.lbm_tape_restore(a.p, tape, j, c.state)
+            got, want = c.export_state(), b.export_state()
+            assert got["step"] == want["step"] == j
+            for k in ("f", "g", "hist"):
+                assert torch.equal(got[k], want[k]), (j, k)
+            b.step(1)
+    finally:
+        os.environ.pop("LBM_TWO_LEVEL", None)
