@@ -836,10 +836,11 @@ static void tape_step2_launch(const KParams<T>& P, char* tape, size_t slot, int 
     else by_store(std::integral_constant<StoreKind, ST_NT>());
 }
 
-// The tiles of the two-level launch of lbm_step (step2_shape).
+// The tiles of the two-level launch of lbm_step, by the same rule (step2_shape; a
+// slot is a copy of the state).
 template <typename T>
 static void tape_step2(const KParams<T>& P, char* tape, size_t slot, int j, hipStream_t s) {
-    switch (step2_shape(P.nx, P.ny, sizeof(T), 2 * slot <= (size_t)LBM_NT_MIN_BYTES)) {
+    switch (step2_shape(P.nx, P.ny, sizeof(T), small_bytes(2 * slot))) {
         case S2_16x4: tape_step2_launch<T, 16, 4, 256>(P, tape, slot, j, s); break;
         case S2_32x4: tape_step2_launch<T, 32, 4, 384>(P, tape, slot, j, s); break;
         case S2_32x8_WIDE: tape_step2_launch<T, 32, 8, 576>(P, tape, slot, j, s); break;
