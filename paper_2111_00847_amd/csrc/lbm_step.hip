@@ -68,18 +68,23 @@ void k_step(KParams<T> P, char* state, size_t off0, size_t off1, size_t off_stam
 // on 64 x 4 threads with two nodes per thread, 4 rows on 64 x 4 below 1024
 // tiles); 16 rows on 64 x 8 threads 575 / 38.2 / 18.4; 16 rows on 64 x 16 656 /
 // 43.2 / 14.0.  LBM_CH_TY forces 4, 8 or 16 rows.
+// SWEEPS: the launches sweep forward and `back` by turns (streamed states).  The steps
+// of cached states do not read `back`: it lies in a cache line of the arguments that
+// nothing else needs, and every workgroup waited for it (FP64 64 x 196 8.77 against
+// 8.55 us per step, 256 x 320 10.3 against 10.0).
 #ifndef LBM_CH_TY
 #define LBM_CH_TY 0
 #endif
 
-template <typename T, int TY, int MODE, bool ACC, bool STD, bool NT = true, int NBY = BY, typename OFF = uint64_t>
+template <typename T, int TY, int MODE, bool ACC, bool STD, bool NT = true, int NBY = BY, typename OFF = uint64_t,
+          bool SWEEPS = true>
 __global__ __launch_bounds__(TX* NBY) void k_step_ch(KParams<T> P, char* state, size_t off0, size_t off1,
                                                     size_t off_stamp, int ntx, int nty, T* out_phi, T* out_u,
                                                     T* out_p, bool back) {
     __shared__ ChWindow<T, TY> W;
     int xt, yt;
     if (LBM_XCD_REMAP) {
-        xcd_tile(blockIdx.x, ntx, nty, xt, yt, back);
+        xcd_tile(blockIdx.x, ntx, nty, xt, yt, SWEEPS && back);
     } else {
         xt = blockIdx.x % ntx;
         yt = blockIdx.x / ntx;
@@ -92,11 +97,11 @@ __global__ __launch_bounds__(TX* NBY) void k_step_ch(KParams<T> P, char* state, 
 constexpr int CH_TY = (LBM_CH_TY == 4 || LBM_CH_TY == 16) ? LBM_CH_TY : 8;
 constexpr int CH_NBY = CH_TY == 4 ? 4 : 8;
 
-template <typename T, int MODE, bool ACC, bool STD, bool NT, typename OFF>
+template <typename T, int MODE, bool ACC, bool STD, bool NT, typename OFF, bool SWEEPS>
 static void launch_ch_shape(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
                             bool back) {
     const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + CH_TY - 1) / CH_TY;
-    k_step_ch<T, CH_TY, MODE, ACC, STD, NT, CH_NBY, OFF><<<ntx * nty, dim3(TX, CH_NBY), 0, s>>>(
+    k_step_ch<T, CH_TY, MODE, ACC, STD, NT, CH_NBY, OFF, SWEEPS><<<ntx * nty, dim3(TX, CH_NBY), 0, s>>>(
         P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, ntx, nty, phi, u, p, back);
 }
 
@@ -105,16 +110,16 @@ static void launch_ch_shape(const KParams<T>& P, char* state, const Layout& L, h
 // FP32 kernel, 62 against 68 VGPRs; measured on MI355X, FP32 square droplet, us
 // per step: 554 against 571 at 4096^2, 37.0 against 39.7 at 1024^2, 7.0 against
 // 9.6 at 200^2); moments and larger copies with 64-bit ones.
-template <typename T, int MODE, bool ACC, bool STD, bool NT = true>
+template <typename T, int MODE, bool ACC, bool STD, bool NT = true, bool SWEEPS = true>
 static void launch_ch_acc_std(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
                               bool back) {
     if constexpr (MODE == 0) {
         if (L.buf_bytes < (size_t(1) << 32)) {
-            launch_ch_shape<T, MODE, ACC, STD, NT, uint32_t>(P, state, L, s, phi, u, p, back);
+            launch_ch_shape<T, MODE, ACC, STD, NT, uint32_t, SWEEPS>(P, state, L, s, phi, u, p, back);
             return;
         }
     }
-    launch_ch_shape<T, MODE, ACC, STD, NT, uint64_t>(P, state, L, s, phi, u, p, back);
+    launch_ch_shape<T, MODE, ACC, STD, NT, uint64_t, true>(P, state, L, s, phi, u, p, back);
 }
 
 // the standard rates compiled in for steps (moments do not collide); steps on
@@ -124,12 +129,14 @@ template <typename T, int MODE, bool ACC>
 static void launch_ch_acc(const KParams<T>& P, char* state, const Layout& L, hipStream_t s, T* phi, T* u, T* p,
                           bool back) {
     if constexpr (MODE == 0) {
-        const bool plain = plain_stores(L, P.nx);
+        const bool plain = plain_stores(L, P.nx), cached = cached_state(L);
         if (P.rates_std) {
-            if (plain) launch_ch_acc_std<T, MODE, ACC, true, false>(P, state, L, s, phi, u, p, back);
+            if (cached) launch_ch_acc_std<T, MODE, ACC, true, false, false>(P, state, L, s, phi, u, p, back);
+            else if (plain) launch_ch_acc_std<T, MODE, ACC, true, false>(P, state, L, s, phi, u, p, back);
             else launch_ch_acc_std<T, MODE, ACC, true>(P, state, L, s, phi, u, p, back);
         } else {
-            if (plain) launch_ch_acc_std<T, MODE, ACC, false, false>(P, state, L, s, phi, u, p, back);
+            if (cached) launch_ch_acc_std<T, MODE, ACC, false, false, false>(P, state, L, s, phi, u, p, back);
+            else if (plain) launch_ch_acc_std<T, MODE, ACC, false, false>(P, state, L, s, phi, u, p, back);
             else launch_ch_acc_std<T, MODE, ACC, false>(P, state, L, s, phi, u, p, back);
         }
     } else {
