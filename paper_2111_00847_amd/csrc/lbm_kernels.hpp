@@ -31,18 +31,26 @@ inline bool stamp_share_ok(int nx, int ny, int tw, int ty) {
 //        256 x 256    32x8 on 576 threads 3.9, 32x4 4.4, 64x8 5.0; one-level 5.74
 //        256 x 512    32x16 5.03, 64x8 5.2, 32x8 5.5
 //        256 x 1024   64x16 6.7, 64x8 6.7, 32x16 6.9
-//        1024 x 512   32x16 12.8, 64x8 13.2, 64x16 13.5; 1024 x 1024 23.1, 23.7, 26.5
-//        4096 x 4096  64x8 364, 32x8 375, 32x16 395 (streamed from HBM)
-//        640 x 1089   32x16 18.2, 64x8 18.8 alone; three lattices at once, more than
-//                     the cache holds, 19.5 and 18.3: 32x16 only for states of which it
-//                     holds three (small_state)
+//        1024 x 512   32x16 12.4, 64x8 12.9; 512 x 700 10.1, 10.6; 700 x 700 12.6, 12.9
+//        640 x 1089   64x8 17.0, 32x16 16.3; three such lattices at once on streams,
+//                     more than the cache holds, 16.7 and 17.4; 1024 x 700 17.4, 16.6
+//                     and 17.8, 17.9; 1024 x 1024 22.7, 22.0 and 25.6, 26.2; 1280 x 1024
+//                     27.5, 27.0 and 32.6, 34.9.  The library does not know what else
+//                     runs: it gives up 2-5% of a lone lattice there, for up to 7% of
+//                     several (small_state)
+//        4096 x 4096  64x8 347, 32x8 375, 32x16 388 (streamed from HBM)
+//        60000 x 3    64x8 10.2, 32x16 16.5; 17000 x 17 12.5, 14.0; 9000 x 49 12.5, 14.5;
+//                     9000 x 40 10.7, 11.7: no tiles of 16 rows on lattices of at most 8, nor
+//                     where they pad it by a sixth more than tiles of 8 or take a round
+//                     more
 //   FP64 64 x 64      16x4 3.67, 32x4 4.3, 64x8 6.9; one-level 9.07
 //        200 x 100    32x4 4.3, 16x4 4.3, 32x8 5.6; one-level 14.5
 //        300 x 300    32x16 7.2, 32x8 7.35, 64x8 7.3
-//        1000 x 500   32x8 24.0, 32x16 26.5, 64x8 27.6; 1999 x 2203 228, 312, 294
+//        1000 x 500   32x8 24.0, 32x16 26.5, 64x8 27.6; 1999 x 2203 194, 312, 294
 // The 32x8 tiles of FP64 (80 KB of LDS) run two workgroups of 256 threads per
 // CU; of one node per thread (576 threads) they serve single-round lattices.
-// S2_NONE: no tile shape has as many stamps as tiles (FP64, one row).
+// S2_NONE: FP64 lattices of one row, which have fewer stamps than 32-wide tiles; they
+// run one level per launch (17000 x 1 7.4, two levels on 64x8 tiles 10.5).
 enum Step2Shape { S2_NONE, S2_16x4, S2_32x4, S2_32x8_WIDE, S2_32x16, S2_64x16, S2_64x8, S2_32x8 };
 inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool small) {
     auto tiles = [&](int tw, int ty) { return (long long)((nx + tw - 1) / tw) * ((ny + ty - 1) / ty); };
@@ -50,10 +58,14 @@ inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool small) {
     if (one_round(16, 4)) return S2_16x4;
     if (one_round(32, 4)) return S2_32x4;
     if (one_round(32, 8)) return S2_32x8_WIDE;
-    if (one_round(32, 16)) return S2_32x16;
+    const bool tall = ny > 8;   // tiles of 16 rows would be half empty
+    if (tall && one_round(32, 16)) return S2_32x16;
     if (esz == 8) return stamp_share_ok(nx, ny, 32, 8) ? S2_32x8 : S2_NONE;
-    if (one_round(64, 16)) return S2_64x16;
-    return small && stamp_share_ok(nx, ny, 32, 16) ? S2_32x16 : S2_64x8;
+    if (tall && one_round(64, 16)) return S2_64x16;
+    const int rows8 = (ny + 7) / 8 * 8, rows16 = (ny + 15) / 16 * 16;
+    auto rounds = [&](int tw, int ty) { return (tiles(tw, ty) + 511) / 512; };   // two workgroups to a CU
+    const bool filled = 6 * rows16 <= 7 * rows8 && rounds(32, 16) <= rounds(64, 8);
+    return small && filled && stamp_share_ok(nx, ny, 32, 16) ? S2_32x16 : S2_64x8;
 }
 
 // the Allen-Cahn step (either gradient scheme, not the corrected model) on a
