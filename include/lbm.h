@@ -162,11 +162,11 @@ int lbm_hydrostatic_pressure(const lbm_params *p, const void *phi0, void *p0, vo
  * the caller's graph instead.  Every option. */
 int lbm_step(const lbm_params *p, void *state, int64_t nsteps, void *stream);
 
-/* Time levels per crossing of the state (1 or 2): 2 where lbm_step folds two
- * levels into a launch on a lattice of at least 256 tiles of 64 x 8 nodes, or on
- * any lattice with LBM_TWO_LEVEL = "1" in the environment.  Smaller lattices
- * report 1: their launches are bound by latency, not by the bytes of a level,
- * and lbm_step folds levels there as it finds best.  Host only, no device work. */
+/* Time levels that a launch of lbm_step advances at least, 1 or 2: 2 where it folds
+ * two levels into a launch on a lattice of at least 256 tiles of 64 x 8 nodes; 1
+ * elsewhere, also on smaller lattices, where lbm_step folds two levels all the same.
+ * With LBM_TWO_LEVEL = "1" in the environment (which changes this answer alone) 2 on
+ * every lattice where it folds two.  Host only, no device work. */
 int lbm_levels_per_launch(const lbm_params *p, int32_t *levels /* host */);
 
 /* Order parameter, velocity (Eq. comU) and pressure (Eq. computP) of the
@@ -310,9 +310,9 @@ int lbm_batch_step(lbm_batch *batch, void *state, int64_t nsteps, void *stream);
  * per launch, work items per step (any pointer may be NULL). */
 int lbm_batch_tuning(const lbm_batch *batch, int32_t *tile_rows, int32_t *thread_rows, int32_t *grid,
                      int32_t *items);
-/* Levels per crossing of the batch state (1 or 2; host *levels), by the rule of
- * lbm_levels_per_launch over all cases' tiles; as there, smaller batches report 1
- * and fold levels as the plan finds best. */
+/* Levels that a launch of the plan advances at least, 1 or 2 (host *levels), by the
+ * rule of lbm_levels_per_launch over all cases' tiles: as there, smaller batches report
+ * 1 and fold two levels all the same. */
 int lbm_batch_levels_per_launch(const lbm_batch *batch, int32_t *levels);
 int lbm_batch_destroy(lbm_batch *batch);
 

@@ -533,10 +533,10 @@ bool two_level_cases(const lbm_params* cases, int ncases) {
     return !(e && e[0] == '0' && e[1] == 0);
 }
 
-// What lbm_batch_levels_per_launch reports: the size rule of a single lattice,
-// at least 256 tiles of 64 x 8 nodes (LBM_TWO_LEVEL=1: whatever the size).
+// What lbm_batch_levels_per_launch reports of a batch that runs two levels per
+// launch: whether it has at least 256 tiles of 64 x 8 nodes (LBM_TWO_LEVEL=1: whatever
+// the size).
 bool two_level_batch(const lbm_params* cases, int ncases) {
-    if (!two_level_cases(cases, ncases)) return false;
     long long tiles8 = 0;
     int ntx, nty;
     for (int c = 0; c < ncases; c++) tiles8 += tiles_for(cases[c], TX, 8, &ntx, &nty);
@@ -717,8 +717,8 @@ int lbm_batch_create(const lbm_params* cases, int32_t ncases, int32_t autotune, 
         B->tuned = true;
     }
     hipError_t e = B->dtype == LBM_F32 ? upload_cases<float>(B, B->ty) : upload_cases<double>(B, B->ty);
-    B->two_level = two_level_batch(cases, ncases);
     B->shape2 = batch_shape2(cases, ncases);
+    B->two_level = B->shape2 != S2_NONE && two_level_batch(cases, ncases);
     B->whole = whole_batch(cases, ncases);
     if (e == hipSuccess && B->shape2 != S2_NONE) e = B->dtype == LBM_F32 ? upload_cases2<float>(B) : upload_cases2<double>(B);
     if (e != hipSuccess) {

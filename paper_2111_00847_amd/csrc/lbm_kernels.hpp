@@ -72,8 +72,8 @@ inline Step2Shape step2_shape(int nx, int ny, size_t esz, bool small) {
 // lattice whose copy fits 32-bit offsets: lbm_step folds two levels into a
 // launch (not with LBM_TWO_LEVEL=0 in the environment)
 bool two_level_step(const Layout& L, int nx, int ny, int pf, int model);
-// the same with the size rule of the 64-wide tiles: what lbm_levels_per_launch
-// reports, and the rule of the batches
+// the same on lattices of at least 256 tiles of 64 x 8 nodes, or on any with
+// LBM_TWO_LEVEL=1: what lbm_levels_per_launch reports
 bool two_level_path(const Layout& L, int nx, int ny, int pf, int model);
 template <typename T>
 hipError_t launch_moments(const KParams<T>& P, const char* state, const Layout& L, T* phi, T* u, T* p,

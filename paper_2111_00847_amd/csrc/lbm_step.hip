@@ -623,10 +623,10 @@ static void launch_tile(const KParams<T>& P, char* state, const Layout& L, hipSt
 // launches are slower on every lattice measured (64 x 64 FP32 4.99 against 3.04
 // us per level, FP64 9.07 against 3.67; 4096 x 4096 523 against 364).  The
 // environment variable LBM_TWO_LEVEL, read at every call, turns it off ("0").
-// lbm_levels_per_launch reports the rule of the 64-wide tiles, at least 256
-// 64 x 8 tiles (every eligible state with LBM_TWO_LEVEL "1"): below it a launch
-// is bound by its own latency, not by the bytes of a level.  The compile-time
-// LBM_TWO_LEVEL=0 removes the path.
+// lbm_levels_per_launch reports 2 only where these launches run, but of those
+// lattices only the ones of at least 256 tiles of 64 x 8 nodes (all of them with
+// LBM_TWO_LEVEL "1", which changes nothing else).  The compile-time LBM_TWO_LEVEL=0
+// removes the path.
 #ifndef LBM_TWO_LEVEL
 #define LBM_TWO_LEVEL 1
 #endif
@@ -645,7 +645,7 @@ bool two_level_step(const Layout& L, int nx, int ny, int pf, int model) {
 }
 
 bool two_level_path(const Layout& L, int nx, int ny, int pf, int model) {
-    if (!two_level_eligible(L, pf, model)) return false;
+    if (!two_level_step(L, nx, ny, pf, model)) return false;
     const long long tiles8 = (long long)((nx + TX - 1) / TX) * ((ny + 7) / 8);
     return two_level_env() == '1' || tiles8 >= 256;
 }
