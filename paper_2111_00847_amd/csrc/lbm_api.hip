@@ -191,7 +191,7 @@ int step_tile_rows(const lbm_params* p) {
 static thread_local char g_last_error[256];
 
 // Captured graphs of GRAPH_K plain steps, reused while (params, state, stream,
-// tile height) match; a small most-recently-used cache.
+// tile height, levels per launch) match; a small most-recently-used cache.
 constexpr int GRAPH_K = 32;
 constexpr size_t GRAPH_CACHE = 256;
 struct StepGraph {
@@ -199,6 +199,7 @@ struct StepGraph {
     void* state;
     hipStream_t stream;
     int ty, by;
+    bool two;             // two-level launches (LBM_TWO_LEVEL is read at every call)
     int copy;             // the copy the graph's first launch expects the state in
     hipGraphExec_t exec;
 };
@@ -325,11 +326,12 @@ int lbm_step(const lbm_params* p, void* state, int64_t nsteps, void* stream) {
         if (e != hipSuccess) return hip_fail(e);
     }
     if (s != nullptr && nsteps >= 2 * GRAPH_K && cs == hipStreamCaptureStatusNone) {
+        const bool two = two_level_step(L, p->nx, p->ny, p->phase_eq, p->model);
         std::lock_guard<std::mutex> lock(g_graph_mu);
         size_t hit = g_graphs.size();
         for (size_t i = 0; i < g_graphs.size(); i++)
             if (g_graphs[i].state == state && g_graphs[i].stream == s && g_graphs[i].ty == ty && g_graphs[i].by == by &&
-                g_graphs[i].copy == copy && memcmp(&g_graphs[i].p, p, sizeof(lbm_params)) == 0) {
+                g_graphs[i].two == two && g_graphs[i].copy == copy && memcmp(&g_graphs[i].p, p, sizeof(lbm_params)) == 0) {
                 hit = i;
                 break;
             }
@@ -345,7 +347,7 @@ int lbm_step(const lbm_params* p, void* state, int64_t nsteps, void* stream) {
             // GRAPH_K is even and so is the launch count of every path: a replay
             // leaves the state in the copy it found it in
             if (c != copy) return hip_fail(hipErrorUnknown);
-            StepGraph sg{*p, state, s, ty, by, copy, nullptr};
+            StepGraph sg{*p, state, s, ty, by, two, copy, nullptr};
             e = hipGraphInstantiate(&sg.exec, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return hip_fail(e);

@@ -40,3 +40,28 @@ def test_batch_with_one_row(dtype):
              for nx, ny in ((20000, 1), (128, 64))]
     assert BatchSim(cases).levels_per_launch() == (2 if dtype == "f32" else 1)
     assert BatchSim([cases[1].replace(nx=1024, ny=512)]).levels_per_launch() == 2
+
+
+@pytest.mark.gpu
+def test_two_level_switch_is_read_at_every_call():
+    """LBM_TWO_LEVEL=0 also stops two-level launches where a graph of them is
+    cached: after one-level launches the other copy of the state holds the level
+    before the last (after two-level ones, the level two before it)."""
+    import torch
+    from paper_2111_00847_amd.sim import Sim
+    case, phi0 = W.square_droplet(n=64, side=32)
+    s = torch.cuda.Stream()
+    a, b = Sim(case, stream=s).init(phi0), Sim(case, stream=s).init(phi0)
+    torch.cuda.synchronize()
+    b.state.copy_(a.state)
+    torch.cuda.synchronize()
+    a.step(64)                # captures and replays a graph of two-level launches
+    os.environ["LBM_TWO_LEVEL"] = "0"
+    try:
+        b.step(64)
+        a.step(64)
+        b.step(64)
+    finally:
+        os.environ.pop("LBM_TWO_LEVEL", None)
+    torch.cuda.synchronize()
+    assert torch.equal(a.state, b.state)
