@@ -37,14 +37,16 @@ struct StateHeader {
 };
 
 // Level stamps.  The time level n of the state and the copy c that holds it
-// are kept per (64-wide column band, row): stamp[xt * ny + y] = 2 n + c.  A
-// step workgroup reads the stamp of its first row to learn n and its source
-// copy, and at its end writes level n + 1 in the other copy into the stamps of
-// the rows it owns (a two-level launch: n + 2 in the other copy, so the copy
-// is not the parity of the level).  Every (band, row) belongs to exactly one
-// workgroup of a launch whatever the tile height, so no two workgroups touch
-// the same stamp and no cross-workgroup synchronisation is needed; all stamps
-// are equal between launches.
+// are kept in one stamp, 2 n + c, per (64-wide column band, row).  A step
+// workgroup reads a stamp that it owns to learn n and its source copy, and at its
+// end writes level n + 1 in the other copy into all of its own (a two-level
+// launch: n + 2 in the other copy, so the copy is not the parity of the level).
+// A one-level launch on 64-wide tiles owns the stamps of its tile's rows,
+// stamp[xt * ny + y]; a two-level launch, whose tiles have other widths, deals them
+// to its tiles in blocks (StampShare).  Either way every stamp belongs to exactly
+// one workgroup of a launch, so no two workgroups touch the same stamp and no
+// cross-workgroup synchronisation is needed; all stamps are equal between
+// launches.
 constexpr int STAMP_BAND = 64;
 __host__ __device__ constexpr int64_t stamp_of(int64_t level, int copy) { return 2 * level + copy; }
 __host__ __device__ constexpr int64_t stamp_level(int64_t s) { return s >> 1; }

@@ -40,26 +40,6 @@ __device__ __forceinline__ float rsqrt_<float>(float x) {
 }
 #endif
 
-// Population i arriving at node (x, y) by pull streaming: it left x - c_i in
-// the previous collision, or -- if x - c_i lies beyond a wall face -- it is the
-// opposite population of (x, y) itself, reflected half-way (Sec. 4 preamble).
-template <typename T>
-__device__ __forceinline__ T pull(const T* __restrict__ src, const KParams<T>& P, int i, int x,
-                                  int y) {
-    int sx = x - cx(i), sy = y - cy(i);
-    bool bb = false;
-    if (sx < 0 || sx >= P.nx) {
-        if (P.wall_x) bb = true;
-        else sx = sx < 0 ? sx + P.nx : sx - P.nx;
-    }
-    if (sy < 0 || sy >= P.ny) {
-        if (P.wall_y) bb = true;
-        else sy = sy < 0 ? sy + P.ny : sy - P.ny;
-    }
-    if (bb) return src[opp(i) * P.plane + (long long)y * P.nx + x];
-    return src[i * P.plane + (long long)sy * P.nx + sx];
-}
-
 // Wetting ghost value for wall k (0: x-, 1: x+, 2: y-, 3: y+) from the first
 // and second fluid nodes of a wall-normal line.  Eq. (Dwetting):
 // a phi_w^2 + b phi_w + c = 0, root -2c / (b + sqrt(b^2 - 4ac)) (the paper's

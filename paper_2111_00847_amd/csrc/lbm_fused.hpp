@@ -156,18 +156,6 @@ __device__ __forceinline__ OFF pull_fg_at(const KParams<T>& P, const char* src, 
     return k;
 }
 
-// Position p of a region on an axis of n nodes -> node index, or -1 where p
-// lies beyond a wall.  Periodic axes wrap (any number of times: a lattice may
-// be narrower than the region).
-__device__ __forceinline__ int region_node(int p, int n, bool wall) {
-    if (p >= 0 && p < n) return p;
-    if (wall) return -1;
-    p = p < 0 ? p + n : p - n;   // one wrap: every lattice at least a few nodes wide
-    if (p >= 0 && p < n) return p;
-    const int r = p % n;
-    return r < 0 ? r + n : r;
-}
-
 // The fused step.  One 64 x TY tile per workgroup of 64 x NBY threads; thread
 // (lx, ly) owns nodes (x0 + lx, y0 + ly + NBY r), r < TY/NBY, keeps their pulled f
 // in registers from the phi pass to the collision, and the ring of the phi

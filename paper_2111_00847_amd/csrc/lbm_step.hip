@@ -214,20 +214,6 @@ __device__ __forceinline__ bool open_neighbourhood(const KParams<T>& P, const T*
     return true;
 }
 
-// mu_phi of a caller field at (x, y) (Sec. 2), positions beyond a wall taking
-// the value of the first fluid node (x first, then y), periodic axes wrapping.
-template <typename T>
-__device__ T mu_at(const KParams<T>& P, const T* phi, int x, int y) {
-    if (x < 0 || x >= P.nx) x = P.wall_x ? (x < 0 ? 0 : P.nx - 1) : (x < 0 ? x + P.nx : x - P.nx);
-    if (y < 0 || y >= P.ny) y = P.wall_y ? (y < 0 ? 0 : P.ny - 1) : (y < 0 ? y + P.ny : y - P.ny);
-    T n_[3][3];
-    for (int j = 0; j < 3; j++)
-        for (int i = 0; i < 3; i++) n_[j][i] = field_at(P, phi, x + i - 1, y + j - 1);
-    T gx, gy, lap;
-    stencil(n_[0][0], n_[0][1], n_[0][2], n_[1][0], n_[1][1], n_[1][2], n_[2][0], n_[2][1], n_[2][2], gx, gy, lap);
-    return chem_pot(P, n_[1][1], lap);
-}
-
 // What a state needs besides its copy: the header and every level stamp.
 struct StateMeta {
     StateHeader* header;
