@@ -193,14 +193,15 @@ __device__ __forceinline__ void step2_body(const BodyParams<T, step2_reload<T>(T
     // position's g follows its f, each once the loads before it are in: all loads of
     // a tile at once leave less time in which one tile's loads run under another's
     // arithmetic.  Elsewhere all f, then all g; three positions to a thread (the FP32
-    // batch's 32 x 8 tiles) by position, and those and FP64 rows of broken lines without
-    // the wait.  Measured on MI355X, us per level, no wait / by position / f then g:
+    // batch's 32 x 8 tiles) and FP64 rows of broken lines (ordinary stores) by position
+    // without the wait.  Measured on MI355X, us per level, no wait / by position / f then g:
     // FP32 4096 x 4096 362 / 346 / 368, 3072 x 2000 137 / 132 / 139, 2048 x 1200 59.6 /
     // 57.5 / 60.1, cached 1280 x 1024 27.7 / 27.4 / 27.1, a batch of 64 cases 95.5 / 94.2 /
-    // 94.5, by position without the wait 93.3; FP64 1999 x 2203 195 / 199 / 196, 3072 x 2000
-    // 274 / 273 / 270, cached 1000 x 700 33.1 / 32.9 / 31.4, 200 x 100 5.3 / 5.05 / 5.0.
+    // 94.5, by position without the wait 93.3; FP64 1999 x 2203 196 / 199 / 197,
+    // by position without the wait 194, 3001 x 2000 268, 264; 3072 x 2000 274 / 273 / 270,
+    // cached 1000 x 700 33.1 / 32.9 / 31.4, 200 x 100 5.3 / 5.05 / 5.0.
     constexpr bool f32 = sizeof(T) == 4, waits = f32 ? S <= 2 : SK != ST_PLAIN;
-    if constexpr (f32 && (SK != ST_THROUGH || S > 2)) {
+    if constexpr (f32 ? SK != ST_THROUGH || S > 2 : SK == ST_PLAIN) {
         each<S>([&](auto index) {
             load_f(index);
             if (waits) wait_loads();
