@@ -71,8 +71,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 ALG_BYTES = {"f32": 168, "f64": 336}   # per lattice update: f, g read+write, (phi, u, v) history read+write
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "k_step2_rti_256x1024_traffic.json")
-# everything the headline's two-level kernel is compiled from (with the build flags)
+# everything the headline's two-level kernel is compiled from (with the build flags), its tile rule among it
 KERNEL_SOURCES = ["paper_2111_00847_amd/csrc/lbm_step2.hip", "paper_2111_00847_amd/csrc/lbm_step2.hpp",
+                  "paper_2111_00847_amd/csrc/lbm_kernels.hpp",
                   "paper_2111_00847_amd/csrc/lbm_fused.hpp", "paper_2111_00847_amd/csrc/lbm_addr.hpp",
                   "paper_2111_00847_amd/csrc/lbm_tile.hpp", "paper_2111_00847_amd/csrc/lbm_device.hpp",
                   "paper_2111_00847_amd/csrc/lbm_common.hpp", "paper_2111_00847_amd/build.py"]
