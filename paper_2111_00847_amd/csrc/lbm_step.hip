@@ -359,8 +359,14 @@ __global__ __launch_bounds__(256) void k_import(KParams<T> P, const T* f, const 
 }
 
 // Post-streaming populations and history of the current level: f, g [9][n],
-// hist [3][n] ([5][n] for the local gradient scheme), any NULL.
-template <typename T, typename OFF>
+// hist [3][n] ([5][n] for the local gradient scheme), any NULL.  Nine loads, then
+// nine stores; in FP64 with non-temporal stores while what is written fits the last-level
+// cache, and beyond it each store after its own load (EACH).  Measured on MI355X, us a
+// call, nine and nine / non-temporal / each: FP64 1024 x 1024 96 / 77 / 99, 1000 x 1001
+// 90 / 77 / 96, 2048 x 1200 183 / 177 / 179, 1999 x 2203 341 / 370 / 313; FP32 3000 x 3001
+// 345 / 357 / 394.
+enum ExportForm { EXPORT_NINE, EXPORT_NT, EXPORT_EACH };
+template <typename T, typename OFF, ExportForm FORM>
 __global__ __launch_bounds__(256) void k_export(KParams<T> P, const char* state, size_t off0, size_t off1,
                                                 size_t off_stamp, T* f, T* g, T* hist) {
     constexpr OFF ES = sizeof(T);
@@ -375,22 +381,25 @@ __global__ __launch_bounds__(256) void k_export(KParams<T> P, const char* state,
         OFF off[9];
         int xi, yi;
         neighbour_offsets<T, OFF, -1>(P, false, x, y, off, xi, yi);
-        if (f) {
-            T v[9];
-            v[0] = (T)rest_decode(S.template ld<T>(off[0], 0), S.template ld<T>(off[0], 18 * plB), P.rest_w);
+        auto give = [&](T* out, T rest, OFF plane0) {
+            if constexpr (FORM == EXPORT_EACH) {
+                out[k] = rest;
 #pragma unroll
-            for (int i = 1; i < Q; i++) v[i] = S.template ld<T>(off[i], pair_plane(i) * plB);
+                for (int i = 1; i < Q; i++) out[i * n + k] = S.template ld<T>(off[i], plane0 + pair_plane(i) * plB);
+            } else {
+                T v[9];
+                v[0] = rest;
 #pragma unroll
-            for (int i = 0; i < Q; i++) f[i * n + k] = v[i];
-        }
-        if (g) {
-            T v[9];
-            v[0] = S.template ld<T>(off[0], 9 * plB);
+                for (int i = 1; i < Q; i++) v[i] = S.template ld<T>(off[i], plane0 + pair_plane(i) * plB);
 #pragma unroll
-            for (int i = 1; i < Q; i++) v[i] = S.template ld<T>(off[i], (9 + pair_plane(i)) * plB);
-#pragma unroll
-            for (int i = 0; i < Q; i++) g[i * n + k] = v[i];
-        }
+                for (int i = 0; i < Q; i++) {
+                    if constexpr (FORM == EXPORT_NT) __builtin_nontemporal_store(v[i], &out[i * n + k]);
+                    else out[i * n + k] = v[i];
+                }
+            }
+        };
+        if (f) give(f, (T)rest_decode(S.template ld<T>(off[0], 0), S.template ld<T>(off[0], 18 * plB), P.rest_w), 0);
+        if (g) give(g, S.template ld<T>(off[0], 9 * plB), 9 * plB);
         if (hist)   // phi, u, v of level n-1 (and m^phiC of level n-1 for the local gradient scheme)
             for (int j = 0; j < nh; j++) hist[j * n + k] = S.template ld<T>(off[0], (18 + j) * plB);
     }
@@ -720,7 +729,9 @@ hipError_t launch_export(const KParams<T>& P, const char* state, const Layout& L
     auto go = [&](auto kernel) LBM_CALLS_STUB {
         kernel<<<grid1d(L.n), 256, 0, s>>>(P, state, L.off_buf[0], L.off_buf[1], L.off_stamp, f, g, hist);
     };
-    small_copy(L) ? go(k_export<T, uint32_t>) : go(k_export<T, uint64_t>);
+    if constexpr (sizeof(T) == 4) small_copy(L) ? go(k_export<T, uint32_t, EXPORT_NINE>) : go(k_export<T, uint64_t, EXPORT_NINE>);
+    else if ((size_t)L.n * (9 * !!f + 9 * !!g + 3 * !!hist) * sizeof(T) <= size_t(256) << 20) go(k_export<T, uint32_t, EXPORT_NT>);
+    else small_copy(L) ? go(k_export<T, uint32_t, EXPORT_EACH>) : go(k_export<T, uint64_t, EXPORT_EACH>);
     return hipGetLastError();
 }
 
