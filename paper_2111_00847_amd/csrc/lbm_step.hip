@@ -521,7 +521,7 @@ __global__ __launch_bounds__(HYDRO_THREADS) void k_hydro_mean(KParams<T> P, T* p
 
 // The same by one workgroup, every thread walking its columns twice (the second
 // walk subtracts the mean the first one gives): for a p0 that overlaps phi0, whose
-// bytes hold no sums before they are read, and for one row.
+// bytes hold no sums before they are read, for one row, and for few rows.
 
 template <typename T>
 __global__ __launch_bounds__(HYDRO_THREADS) void k_hydrostatic(KParams<T> P, const T* phi0, T* p0) {
@@ -700,7 +700,13 @@ hipError_t launch_init(const KParams<T>& P, char* state, const Layout& L, const 
 template <typename T>
 hipError_t launch_hydrostatic(const KParams<T>& P, const T* phi0, T* p0, hipStream_t s) {
     const long long n = (long long)P.nx * P.ny;
-    if (P.ny < 2 || (p0 < phi0 + n && phi0 < p0 + n)) {
+    // One workgroup where it walks few rows in all (its columns 1024 at a time, about 0.25
+    // us a row), less than the three launches of the staged columns take (14 us, and more
+    // from 16 passes on): 48 x 40 13.0 against 15.3 us, 1000 x 30 13.4 / 14.3, 20000 x 2 17.2 /
+    // 31.8; 48 x 50 15.5 / 15.0, 1000 x 40 16.9 / 14.4, 4000 x 10 17.0 / 14.1.  Same bits.
+    const long long passes = (P.nx + HYDRO_THREADS - 1) / HYDRO_THREADS;
+    const bool few = passes * P.ny <= (P.nx <= 256 ? 40 : 28 + 2 * passes);
+    if (P.ny < 2 || few || (p0 < phi0 + n && phi0 < p0 + n)) {
         k_hydrostatic<T><<<1, HYDRO_THREADS, 0, s>>>(P, phi0, p0);
         return hipGetLastError();
     }
