@@ -108,12 +108,19 @@ static int ghost_blocks(const lbm_params* p);
 //   96 x 48 FP64 22.0 / 52.9, FP32 20.3 / 25.3; 256 x 128 FP64 25.4 / 60.1
 //   1024 x 512 FP64 89.1 (32 x 4 90.2, 64 x 8 90.2) / 170.6, FP32 48.8 (53.0, 49.8) / 49.5
 //   2048 x 1024 FP32 160 (172, 163) / 177
+// 32 x 4 also on lattices no wider, which 64-wide tiles would half pad (64 x 4 in
+// brackets): 20 x 4000 FP32 23.1 (26.2) / 25.3, 30 x 6000 FP64 44.7 (56.9) / 95.2.  FP32
+// lattices that 64 x 8 tiles fill for one or two rounds take those: 256 x 1024 30.2 (30.9) /
+// 29.5, 512 x 512 32.7 (33.3) / 32.2, 256 x 500 27.3 (27.6) / 30.8; between full rounds 64 x 4
+// is better (700 x 400 39.4, 64 x 8 40.2).
 struct AdjTile {
     int w, h;
 };
-static AdjTile adj_tile(int nx, int ny) {
-    const long long t = (long long)((nx + 31) / 32) * ((ny + 3) / 4);
-    return t <= 512 ? AdjTile{32, 4} : AdjTile{64, 4};
+static AdjTile adj_tile(int nx, int ny, size_t esz) {
+    auto tiles = [&](int w, int h) { return (long long)((nx + w - 1) / w) * ((ny + h - 1) / h); };
+    if (nx <= 32 || tiles(32, 4) <= 512) return AdjTile{32, 4};
+    const long long t8 = tiles(64, 8), idle = (256 - t8 % 256) % 256;
+    return esz == 4 && t8 <= 512 && idle <= 12 ? AdjTile{64, 8} : AdjTile{64, 4};
 }
 
 AdjLayout adj_layout_of(const lbm_params* p) {
@@ -128,7 +135,7 @@ AdjLayout adj_layout_of(const lbm_params* p) {
     A.off_edge = A.off_scr + (size_t)S_COUNT * L.plane * L.esz;
     A.emax = ((long long)(p->nx > p->ny ? p->nx : p->ny) + 63) / 64 * 64;
     A.off_part = al256(A.off_edge + (size_t)16 * A.emax * L.esz);
-    const AdjTile t = adj_tile(p->nx, p->ny);
+    const AdjTile t = adj_tile(p->nx, p->ny, L.esz);
     A.ntA = ((p->nx + t.w - 1) / t.w) * ((p->ny + t.h - 1) / t.h);
     A.ntB = ((p->nx + TX - 1) / TX) * ((p->ny + BTY - 1) / BTY);
     A.nB = ghost_blocks(p);   // workgroups of kernel G
@@ -884,9 +891,13 @@ static void launch_adj_step(const KParams<T>& P, const char* tape, size_t slot, 
         if (small) k32<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
         else k64<<<V.ntA, nt, 0, s>>>(P, tape, slot, j, V);
     };
-    if (adj_tile(P.nx, P.ny).w == 32)
+    const AdjTile tile = adj_tile(P.nx, P.ny, sizeof(T));
+    if (tile.w == 32)
         a_launch(k_adj_local<T, uint32_t, 32, 4, true>, k_adj_local<T, uint64_t, 32, 4, true>, 128);
-    else a_launch(k_adj_local<T, uint32_t, 64, 4, false>, k_adj_local<T, uint64_t, 64, 4, false>, 256);
+    else if (tile.h == 4)
+        a_launch(k_adj_local<T, uint32_t, 64, 4, false>, k_adj_local<T, uint64_t, 64, 4, false>, 256);
+    else if constexpr (sizeof(T) == 4)   // far below 4 GiB
+        a_launch(k_adj_local<T, uint32_t, 64, 8, false>, k_adj_local<T, uint32_t, 64, 8, false>, 512);
     if (small) {
         if (P.wall_x || P.wall_y) k_adj_ghosts<T, uint32_t><<<V.nB, GHOST_THREADS, 0, s>>>(P, tape, slot, j, V);
         k_adj_gather<T, uint32_t><<<V.ntB, dim3(TX, BY), 0, s>>>(P, tape, j, V);
