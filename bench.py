@@ -308,7 +308,7 @@ def measure_local(args, torch, W, Sim):
     torch.cuda.empty_cache()
     return {"workload": "rayleigh_taylor_4096x4096_local_gradient", "dtype": "f32", "steps": steps,
             "value": round(case.nodes * steps / (ms * 1e-3) / 1e6, 1), "unit": "MLUPS",
-            "kernel": "k_step2_local<float> (two levels per launch)" if levels == 2 else "k_step_local<float>",
+            "kernel": "k_step2<float, local gradient> (two levels per launch)" if levels == 2 else "k_step_local<float>",
             "levels_per_launch": levels, "achieved_GBs": round(ach, 1), "frac": round(ach / HBM_PEAK_GBS, 4),
             "avg_level_ms": round(ms / steps, 4),
             "one_level": {"kernel": "k_step_local<float>", "value": round(case.nodes * steps / (ms1 * 1e-3) / 1e6, 1),

@@ -561,7 +561,8 @@ bool whole_batch(const lbm_params* cases, int ncases) {
 // MI355X, us per level, spreading cases of 128 x 64 to 512 x 256 nodes, 32x8 /
 // 64x8 / 32x16: FP32 3 cases 7.0 / 7.6 / 7.3, 8 cases 13.6 / 13.4 / 12.8, 20 cases
 // 30.1 / 31.6 / 30.6, 64 cases (streamed) 100.6 / 102.2 / 111.7; FP64 3 cases 12.1 /
-// 14.4 / 13.8, 8 cases 26.1 / 28.6 / 27.9, 64 cases 213.6 / 252.2 / 258.6.
+// 14.4 / 13.8, 8 cases 26.1 / 28.6 / 27.9, 64 cases 213.6 / 252.2 / 258.6.  32x8 beyond one
+// round although 32x16 is 6% faster at 8 FP32 cases: at 3 and 20 it is 2-4% slower, at 64 11%.
 Step2Shape batch_shape2(const lbm_params* cases, int ncases) {
     if (!two_level_cases(cases, ncases)) return S2_NONE;
     bool shares = true;
